@@ -143,7 +143,7 @@ __global__ void __launch_bounds__(kMemoThreads) lexmemo_kernel(DevTab tb, uint4*
 struct WsArgs {
   char* base;
   size_t slot_bytes;
-  size_t off_cnt, off_org, off_sn, off_st, off_bits, off_cov;
+  size_t off_cnt, off_org, off_pn, off_bits, off_cov;
   int maxn, maxe, nslot, base_slots, max_seq;
   size_t snap_off, snap_bytes, bseq_off;
 };
@@ -154,8 +154,7 @@ __device__ inline WgWork slot_work(const WsArgs& a, int slot) {
   w.row_off = (int32_t*)b;
   w.row_cnt = (int32_t*)(b + a.off_cnt);
   w.ent_org = (int32_t*)(b + a.off_org);
-  w.ent_sn = (uint64_t*)(b + a.off_sn);
-  w.ent_st = (uint64_t*)(b + a.off_st);
+  w.row_pn = (uint64_t*)(b + a.off_pn);
   w.ent_bits = (uint32_t*)(b + a.off_bits);
   w.cov = (uint32_t*)(b + a.off_cov);
   w.maxn = a.maxn;
@@ -163,8 +162,7 @@ __device__ inline WgWork slot_work(const WsArgs& a, int slot) {
   w.b_row_off = w.row_off;
   w.b_row_cnt = w.row_cnt;
   w.b_ent_org = w.ent_org;
-  w.b_ent_sn = w.ent_sn;
-  w.b_ent_st = w.ent_st;
+  w.b_row_pn = w.row_pn;
   w.b_ent_bits = w.ent_bits;
   w.b_cov = w.cov;
   w.split_node = 0;
@@ -198,15 +196,13 @@ EPIC_INLINE void resume_from_base(Lds<W>& L, const WsArgs& a, int rec, int run, 
   }
   const int nc = nn < Lds<W>::kNodeCache ? nn : Lds<W>::kNodeCache;
   for (int v = t0; v < nc; v += NT) {
-    const int c = base.row_cnt[v];
     L.n_off[v] = base.row_off[v];
-    L.n_cnt[v] = (int16_t)((c & kCntMask) | ((c & kOwnFlag) ? 0x8000 : 0));
+    L.n_cnt[v] = mirror_cnt(base.row_cnt[v]);
   }
   w.b_row_off = base.row_off;
   w.b_row_cnt = base.row_cnt;
   w.b_ent_org = base.ent_org;
-  w.b_ent_sn = base.ent_sn;
-  w.b_ent_st = base.ent_st;
+  w.b_row_pn = base.row_pn;
   w.b_ent_bits = base.ent_bits;
   w.b_cov = base.cov;
   w.split_node = nn;
@@ -283,9 +279,9 @@ EPIC_INLINE void base_body(const DevTab& tb, Lds<W>& L, const int32_t* __restric
   }
   publish_record(L, snap, (uint32_t)(r0 >= 0 ? r0 : 0));  // snapshots before r0 stay as they are
   if (cov)
-    walk<W, W, true>(tb, L, wk, n, i0, r0 >= 0, snap, r0 >= 0 ? r0 : 0);
+    walk<W, true>(tb, L, wk, n, i0, r0 >= 0, snap, r0 >= 0 ? r0 : 0);
   else
-    walk<W, W, false>(tb, L, wk, n, i0, r0 >= 0, snap, r0 >= 0 ? r0 : 0);
+    walk<W, false>(tb, L, wk, n, i0, r0 >= 0, snap, r0 >= 0 ? r0 : 0);
 }
 
 template <int W, int NT>
@@ -380,17 +376,17 @@ EPIC_INLINE void validate_body(const DevTab& tb, Lds<W>& L, const int32_t* __res
       }
       const int status = ready == 1 ? h[0] : 0, runs = ready == 1 ? h[1] : run + 1;
       if (ready == 0) {
-        r = walk<W, W, false>(tb, L, wk, n);
+        r = walk<W, false>(tb, L, wk, n);
       } else if (run < runs) {
         WgWork wr = wk;
         resume_from_base<W>(L, ws, b, run, wr);
-        r = walk<W, W, false>(tb, L, wr, n, p0, true);
+        r = walk<W, false>(tb, L, wr, n, p0, true);
       } else {
         r = status == 1 ? 0 : -1;  // the shared prefix died, or overflowed
         if (threadIdx.x == 0 && r < 0) L.overflow = kOvEntries;
       }
     } else {
-      r = walk<W, W, false>(tb, L, wk, n);
+      r = walk<W, false>(tb, L, wk, n);
     }
     if (threadIdx.x == 0) {
       verdict[c] = (uint8_t)(r < 0 ? 2 : r);
@@ -703,7 +699,7 @@ EPIC_INLINE int select_walk_body(const DevTab& tb, Lds<W>& L, const WgWork& wk, 
                            const int32_t* __restrict__ seqs, int n, int b, uint64_t msk) {
   select_apply<W>(L, seqs, n, b, msk);
   if constexpr (!SHARE) {
-    return walk<W, W, COVER>(tb, L, wk, n);
+    return walk<W, COVER>(tb, L, wk, n);
   } else {
   WgWork wr = wk;
   int p0 = 0;
@@ -738,7 +734,7 @@ EPIC_INLINE int select_walk_body(const DevTab& tb, Lds<W>& L, const WgWork& wk, 
     resume_from_base<W>(L, ws, rec, run, wr);
     resume = true;
   }
-  return walk<W, W, COVER>(tb, L, wr, n, resume ? p0 : 0, resume);
+  return walk<W, COVER>(tb, L, wr, n, resume ? p0 : 0, resume);
   }
 }
 
@@ -1241,7 +1237,7 @@ struct epic_ctx {
   int max_batch = 0, max_seq = 0, max_cands = 0;
   int maxn = 0, maxe = 0, nslot = 0;
   size_t slot_bytes = 0, ws_bytes = 0;
-  size_t off_cnt = 0, off_org = 0, off_sn = 0, off_st = 0, off_bits = 0, off_cov = 0;
+  size_t off_cnt = 0, off_org = 0, off_pn = 0, off_bits = 0, off_cov = 0;
   void* d_tables = nullptr;
   uint4* d_memo = nullptr;
   uint32_t* d_err = nullptr;
@@ -1348,11 +1344,11 @@ epic_status upload(epic_ctx* c) {
   size_t o_trans = place(blob, H.trans), o_accept = place(blob, H.accept), o_ext = place(blob, H.ext),
          o_flush = place(blob, H.flushlab), o_cexit = place(blob, H.cls_exit), o_cint = place(blob, H.cls_internal),
          o_centry = place(blob, H.cls_entry), o_cflush = place(blob, H.cls_flush), o_expt = place(blob, H.exp_t),
-         o_expn = place(blob, H.exp_n), o_pred = place(blob, H.pred), o_comp = place(blob, H.complete),
-         o_lhs = place(blob, H.item_lhs), o_nsym = place(blob, H.next_sym), o_mn = place(blob, H.mn),
+         o_comp = place(blob, H.complete), o_nsym = place(blob, H.next_sym), o_mn = place(blob, H.mn),
          o_gtm = place(blob, H.gap_tm), o_gown = place(blob, H.gap_own), o_ccl = place(blob, H.cover_cl),
          o_enib = place(blob, H.expn_nib), o_pnib = place(blob, H.pred_nib), o_gcov = place(blob, H.gap_cover),
-         o_lnib = place(blob, H.lhs_nib), o_snib = place(blob, H.sym_nib), o_psnib = place(blob, H.predsym_nib), o_plan = place(blob, speculation_plan()),
+         o_lnib = place(blob, H.lhs_nib), o_pnnib = place(blob, H.prednt_nib), o_cas1 = place(blob, H.cas1),
+         o_cas = place(blob, H.cas), o_plan = place(blob, speculation_plan()),
          o_vb = place(blob, H.vbytes), o_vo = place(blob, H.voffs), o_endof = place(blob, H.end_of),
          o_dot0 = place(blob, H.dot0), o_wynt = place(blob, H.wy_nt), o_wyown = place(blob, H.wy_own),
          o_wypool = place(blob, H.wy_pool);
@@ -1404,10 +1400,7 @@ epic_status upload(epic_ctx* c) {
   t.cls_entry = (const uint64_t*)(d + o_centry);
   t.cls_flush = (const uint64_t*)(d + o_cflush);
   t.exp_t = (const uint32_t*)(d + o_expt);
-  t.exp_n = (const uint32_t*)(d + o_expn);
-  t.pred = (const uint32_t*)(d + o_pred);
   t.complete = (const uint32_t*)(d + o_comp);
-  t.item_lhs = (const int8_t*)(d + o_lhs);
   t.next_sym = (const int8_t*)(d + o_nsym);
   t.mn = (const uint32_t*)(d + o_mn);
   t.gap_tm = (const uint32_t*)(d + o_gtm);
@@ -1417,8 +1410,10 @@ epic_status upload(epic_ctx* c) {
   t.pred_nib = (const uint32_t*)(d + o_pnib);
   t.gap_cover = (const uint32_t*)(d + o_gcov);
   t.lhs_nib = (const uint64_t*)(d + o_lnib);
-  t.sym_nib = (const uint64_t*)(d + o_snib);
-  t.predsym_nib = (const uint64_t*)(d + o_psnib);
+  t.prednt_nib = (const uint64_t*)(d + o_pnnib);
+  t.cas1 = (const uint64_t*)(d + o_cas1);
+  t.cas = (const uint64_t*)(d + o_cas);
+  t.gap_own_any = H.gap_own_any;
   t.plan = (const int32_t*)(d + o_plan);
   t.cover_cl = (const uint32_t*)(d + o_ccl);
   t.vbytes = (const uint8_t*)(d + o_vb);
@@ -1441,8 +1436,7 @@ WsArgs ws_args(const epic_ctx* c, void* ws) {
   a.slot_bytes = c->slot_bytes;
   a.off_cnt = c->off_cnt;
   a.off_org = c->off_org;
-  a.off_sn = c->off_sn;
-  a.off_st = c->off_st;
+  a.off_pn = c->off_pn;
   a.off_bits = c->off_bits;
   a.off_cov = c->off_cov;
   a.maxn = c->maxn;
@@ -1603,8 +1597,9 @@ epic_status ValidateLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int 
                        n, c->tag, gb, cs, cp, ct, C, verdict, wa, c->epoch, tab_for(c, kKBase).work);
   } else if (W >= 16 && grid <= c->num_cus) {
     KernelTimer kt(c, kKValidate, stream);
-    hipLaunchKernelGGL((validate_kernel<W, kThreadsWide, false>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
-                       B, n, cs, cp, ct, C, verdict, wa);
+    if constexpr (W >= 16)
+      hipLaunchKernelGGL((validate_kernel<W, kThreadsWide, false>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
+                         B, n, cs, cp, ct, C, verdict, wa);
   } else {
     KernelTimer kt(c, kKValidate, stream);
     hipLaunchKernelGGL((validate_kernel<W, kThreads, false>), dim3(grid), dim3(kThreads), 0, stream, tb, seqs, B, n, cs,
@@ -1646,10 +1641,11 @@ epic_status SelectLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int n,
   const DevTab tb = tab_for(c, kKSelect);
   {
     KernelTimer kt(c, kKSelect, stream);
-    if (wide)
-      hipLaunchKernelGGL((select_kernel<W, kThreadsWide, false>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
-                         B, n, cs, cp, ct, conf, verdict, C, sel, (long long*)counts, spec, wa);
-    else if (share)
+    if (wide) {
+      if constexpr (W >= 16)
+        hipLaunchKernelGGL((select_kernel<W, kThreadsWide, false>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
+                           B, n, cs, cp, ct, conf, verdict, C, sel, (long long*)counts, spec, wa);
+    } else if (share)
       hipLaunchKernelGGL((select_kernel<W, kThreads, true>), dim3(grid), dim3(kThreads), 0, stream, tb, seqs, B, n,
                          cs, cp, ct, conf, verdict, C, sel, (long long*)counts, spec, wa);
     else
@@ -1705,10 +1701,11 @@ epic_status ValidatePlainLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B,
   wa.base_slots = 0;
   const int grid = std::min(C, nslot);
   const DevTab tb = tab_for(c, kKValidate);
-  if (W >= 16 && grid <= c->num_cus)
-    hipLaunchKernelGGL((validate_kernel<W, kThreadsWide, false>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
-                       B, n, cs, cp, ct, C, verdict, wa);
-  else
+  if (W >= 16 && grid <= c->num_cus) {
+    if constexpr (W >= 16)
+      hipLaunchKernelGGL((validate_kernel<W, kThreadsWide, false>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
+                         B, n, cs, cp, ct, C, verdict, wa);
+  } else
     hipLaunchKernelGGL((validate_kernel<W, kThreads, false>), dim3(grid), dim3(kThreads), 0, stream, tb, seqs, B, n, cs,
                        cp, ct, C, verdict, wa);
   return hipGetLastError() == hipSuccess ? EPIC_OK : EPIC_ERR_HIP;
@@ -1943,9 +1940,8 @@ epic_status epic_ctx_create(const epic_lexer_desc* lexer, const epic_grammar_des
   c->nslot = std::min(std::max(max_cands, max_batch), 1024);
   c->off_cnt = align256((size_t)c->maxn * 4);
   c->off_org = c->off_cnt + align256((size_t)c->maxn * 4);
-  c->off_sn = c->off_org + align256((size_t)c->maxe * 4);
-  c->off_st = c->off_sn + align256((size_t)c->maxe * 8);
-  c->off_bits = c->off_st + align256((size_t)c->maxe * 8);
+  c->off_pn = c->off_org + align256((size_t)c->maxe * 4);
+  c->off_bits = c->off_pn + align256((size_t)c->maxn * 8);
   c->off_cov = c->off_bits + align256((size_t)c->maxe * H.W * 4);
   c->slot_bytes = c->off_cov + align256((size_t)c->maxn * H.CW * 4);
   c->base_slots = std::min(max_batch, 1024);

@@ -462,7 +462,6 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
         }
       }
   H.lhs_nib.assign((size_t)W * 8 * 16, 0);
-  H.sym_nib.assign((size_t)W * 8 * 16 * 2, 0);
   for (int w = 0; w < W; ++w)
     for (int j = 0; j < 8; ++j)
       for (int v = 0; v < 16; ++v)
@@ -471,21 +470,13 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
           const int it = w * 32 + 4 * j + b;
           const size_t e = ((size_t)w * 8 + j) * 16 + v;
           if (((H.complete[w] >> (4 * j + b)) & 1) && H.item_lhs[it] >= 0) H.lhs_nib[e] |= 1ull << H.item_lhs[it];
-          const int sym = H.next_sym[it];
-          if (sym >= 64)
-            H.sym_nib[2 * e] |= 1ull << (sym - 64);
-          else if (sym >= 0)
-            H.sym_nib[2 * e + 1] |= 1ull << sym;
         }
-  H.predsym_nib.assign((size_t)16 * 16 * 2, 0);
+  H.prednt_nib.assign((size_t)16 * 16, 0);
   for (int e = 0; e < 16 * 16; ++e)
     for (int w = 0; w < W; ++w)
       for (uint32_t bits = H.pred_nib[(size_t)e * W + w]; bits; bits &= bits - 1) {
         const int sym = H.next_sym[w * 32 + __builtin_ctz(bits)];
-        if (sym >= 64)
-          H.predsym_nib[2 * e] |= 1ull << (sym - 64);
-        else if (sym >= 0)
-          H.predsym_nib[2 * e + 1] |= 1ull << sym;
+        if (sym >= 64) H.prednt_nib[e] |= 1ull << (sym - 64);
       }
 
   // ---------------------------------------------------------------- cover
@@ -797,6 +788,74 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
     }
     for (int k = 0; k < K; ++k)
       for (int w = 0; w < W; ++w) H.gap_own[((size_t)j * K + k) * W + w] = x[k][w];
+  }
+  H.gap_own_any = 0;
+  for (int jk = 0; jk < K * K; ++jk)
+    for (int w = 0; w < W; ++w)
+      if (H.gap_own[(size_t)jk * W + w]) H.gap_own_any |= 1ull << jk;
+  // ---------------------------------------------------------------- completion cascades
+  auto completed = [&](const Set& x) {
+    uint64_t c = 0;
+    for (int i = 0; i < ni; ++i)
+      if (((x[i >> 5] & H.complete[i >> 5]) >> (i & 31)) & 1)
+        if (H.item_lhs[i] >= 0) c |= 1ull << H.item_lhs[i];
+    return c;
+  };
+  H.cas1.assign((size_t)(1 + K) * kMaxNonterminals, 0);
+  H.cas.assign(K <= 2 ? (size_t)(1 + K) * KK * kMaxNonterminals * KK : 0, 0);
+  for (int type = 0; type <= K; ++type) {
+    Set y(W, 0);  // the origin's own entry
+    if (type == 0) {
+      for (int B = 0; B < N; ++B)
+        for (int w = 0; w < W; ++w) y[w] |= H.start_of[(size_t)B * W + w];
+      nclose(y);
+    } else {
+      for (int w = 0; w < W; ++w) y[w] = H.gap_own[((size_t)(type - 1) * K + type - 1) * W + w];
+    }
+    for (int A = 0; A < N; ++A) {
+      uint64_t c = 1ull << A;
+      for (uint64_t before = 0; c != before;) {
+        before = c;
+        Set x(W, 0);
+        adv_or(y, exp_mask(c), x);
+        nclose(x);
+        c |= completed(x);
+      }
+      H.cas1[(size_t)type * kMaxNonterminals + A] = c;
+      if (K > 2) continue;
+      for (int j = 0; j < K; ++j) {
+        std::vector<uint64_t> ck(K, 0);
+        ck[j] = 1ull << A;
+        for (bool changed = true; changed;) {
+          changed = false;
+          std::vector<Set> x(K, Set(W, 0));
+          for (int k = 0; k < K; ++k) adv_or(y, exp_mask(ck[k]), x[k]);
+          for (bool moved = true; moved;) {
+            moved = false;
+            for (int a = 0; a < K; ++a)
+              for (int b = 0; b < K; ++b) {
+                Set m(H.gap_tm.begin() + ((size_t)a * K + b) * W, H.gap_tm.begin() + ((size_t)a * K + b + 1) * W);
+                if (adv_or(x[a], m, x[b])) moved = true;
+                if (a != b && epsp[(size_t)a * K + b])
+                  for (int w = 0; w < W; ++w)
+                    if (x[a][w] & ~x[b][w]) {
+                      x[b][w] |= x[a][w];
+                      moved = true;
+                    }
+              }
+          }
+          for (int k = 0; k < K; ++k) {
+            const uint64_t c2 = completed(x[k]);
+            if (c2 & ~ck[k]) {
+              ck[k] |= c2;
+              changed = true;
+            }
+          }
+        }
+        for (int k = 0; k < K; ++k)
+          H.cas[(((size_t)type * K + j) * kMaxNonterminals + A) * K + k] = ck[k];
+      }
+    }
   }
   // ---------------------------------------------------------------- witness strings
   H.dot0.assign(W, 0);

@@ -36,6 +36,16 @@ struct HostTables {
   uint64_t gap_eps = 0;           // bit j*K+k: class k reachable from class j by epsilon edges
   std::vector<uint32_t> gap_tm;   // [K*K*W] items that advance from class j to class k
   std::vector<uint32_t> gap_own;  // [K*K*W] entry of the run's origin j at class k
+  uint64_t gap_own_any = 0;       // bit j*K+k: that entry is not empty
+  // Completion cascades at one origin: the nonterminals completed, A among
+  // them, when A completes and the origin's own entry advances over it and over
+  // all that this completes in turn.  Origin type 0: a single node that
+  // predicts every production; 1 + i: class node i of a masked run (its own
+  // entry gap_own[i][i]).  cas1[type*64 + A]: at a single node.
+  // cas[((type*K + j)*64 + A)*K + k]: in a masked run of at most two class
+  // nodes, A completing at class j, those completed at class k.
+  std::vector<uint64_t> cas1;
+  std::vector<uint64_t> cas;
   // grammar (dotted items numbered per production, consecutively)
   std::vector<uint32_t> exp_t;     // [T*W] items whose next symbol is terminal a
   std::vector<uint32_t> exp_n;     // [N*W] items whose next symbol is nonterminal B
@@ -51,13 +61,10 @@ struct HostTables {
   std::vector<uint32_t> expn_nib;  // [16*16*W]
   std::vector<uint32_t> pred_nib;  // [16*16*W]
   // per item word w and nibble j (bits 4j..4j+3) of it, indexed by the nibble's
-  // value: the nonterminals completed by its end items (lhs_nib), and the
-  // nonterminals and terminals its items expect (sym_nib: pairs of words)
+  // value: the nonterminals completed by its end items
   std::vector<uint64_t> lhs_nib;  // [W*8*16]
-  std::vector<uint64_t> sym_nib;  // [W*8*16*2]
-  // the nonterminals and terminals expected by the items of pred_nib's entry
-  // (i, v), pairs of words: the symbols a prediction closure expects
-  std::vector<uint64_t> predsym_nib;  // [16*16*2]
+  // the nonterminals expected by the items of pred_nib's entry (i, v)
+  std::vector<uint64_t> prednt_nib;  // [16*16]
   std::vector<uint32_t> start_of;  // [N*W] items A -> . gamma
   std::vector<uint32_t> end_of;    // [N*W] items A -> gamma .
   // regular cover: state bit i < 32W is dotted item i (rule position), bit 32W+A is
