@@ -143,28 +143,13 @@ __global__ void __launch_bounds__(kMemoThreads) lexmemo_kernel(DevTab tb, uint4*
 struct WsArgs {
   char* base;
   size_t slot_bytes;
-  size_t off_cnt, off_org, off_pn, off_bits, off_cov;
-  int maxn, maxe, nslot, base_slots, max_seq;
+  int nslot, base_slots, max_seq;
   size_t snap_off, snap_bytes, bseq_off;
 };
 
 __device__ inline WgWork slot_work(const WsArgs& a, int slot) {
-  char* b = a.base + (size_t)slot * a.slot_bytes;
   WgWork w;
-  w.row_off = (int32_t*)b;
-  w.row_cnt = (int32_t*)(b + a.off_cnt);
-  w.ent_org = (int32_t*)(b + a.off_org);
-  w.row_pn = (uint64_t*)(b + a.off_pn);
-  w.ent_bits = (uint32_t*)(b + a.off_bits);
-  w.cov = (uint32_t*)(b + a.off_cov);
-  w.maxn = a.maxn;
-  w.maxe = a.maxe;
-  w.b_row_off = w.row_off;
-  w.b_row_cnt = w.row_cnt;
-  w.b_ent_org = w.ent_org;
-  w.b_row_pn = w.row_pn;
-  w.b_ent_bits = w.ent_bits;
-  w.b_cov = w.cov;
+  w.base = w.bbase = a.base + (size_t)slot * a.slot_bytes;
   w.split_node = 0;
   w.split_ent = 0;
   w.rec = nullptr;
@@ -177,8 +162,8 @@ __device__ inline char* snap_record(const WsArgs& a, int b) { return a.base + a.
 // counters, row mirrors of the shared nodes) and point w's reads of the
 // shared prefix at the base chart.
 template <int W>
-EPIC_INLINE void resume_from_base(Lds<W>& L, const WsArgs& a, int rec, int run, WgWork& w) {
-  const WgWork base = slot_work(a, a.nslot + rec);
+EPIC_INLINE void resume_from_base(Tab& tb, Lds<W>& L, const WsArgs& a, int rec, int run, WgWork& w) {
+  char* const base = slot_work(a, a.nslot + rec).base;
   const Snapshot* sp = reinterpret_cast<const Snapshot*>(snap_record(a, rec) + kSnapHeader) + run;
   const int t0 = threadIdx.x, NT = blockDim.x;
   const int nn = sp->next_node, ne = sp->ent_cursor, nf = sp->fr_n;
@@ -196,15 +181,10 @@ EPIC_INLINE void resume_from_base(Lds<W>& L, const WsArgs& a, int rec, int run, 
   }
   const int nc = nn < Lds<W>::kNodeCache ? nn : Lds<W>::kNodeCache;
   for (int v = t0; v < nc; v += NT) {
-    L.n_off[v] = base.row_off[v];
-    L.n_cnt[v] = mirror_cnt(base.row_cnt[v]);
+    L.n_off[v] = chart_row_off(base)[v];
+    L.n_cnt[v] = mirror_cnt(chart_row_cnt(tb, base)[v]);
   }
-  w.b_row_off = base.row_off;
-  w.b_row_cnt = base.row_cnt;
-  w.b_ent_org = base.ent_org;
-  w.b_row_pn = base.row_pn;
-  w.b_ent_bits = base.ent_bits;
-  w.b_cov = base.cov;
+  w.bbase = base;
   w.split_node = nn;
   w.split_ent = ne;
   __syncthreads();
@@ -220,12 +200,25 @@ EPIC_INLINE void resume_from_base(Lds<W>& L, const WsArgs& a, int rec, int run, 
 // the first token that differs from the sequence the record was walked on
 // (the token there is then walked as the sequence now has it), and a record
 // of the very same sequence is kept as it is.
-// Base walk number blk (blk < B: the Earley graph of sequence blk; else the
-// cover graph of sequence blk - B).  With a nonzero epoch the record's
+// A walk to be made (see walk()): its chart, and where it starts.
+struct WalkPlan {
+  WgWork wk;
+  bool cover, resume;
+  int i0, run0;
+  char* snap;
+};
+template <int W>
+EPIC_INLINE int run_walk(Tab& tb, Lds<W>& L, const WalkPlan& p, int n) {
+  return walk<W>(tb, L, p.wk, n, p.cover, p.i0, p.resume, p.snap, p.run0);
+}
+
+// Prepare base walk number blk (blk < B: the Earley graph of sequence blk;
+// else the cover graph of sequence blk - B).  With a nonzero epoch the record's
 // progress is published for walks of the same launch (publish_record).
+// Returns false when there is nothing to walk.
 template <int W, int NT>
-EPIC_INLINE void base_body(const DevTab& tb, Lds<W>& L, const int32_t* __restrict__ seqs, int B, int n, uint64_t tag,
-                           const WsArgs& ws, int blk, uint32_t epoch) {
+EPIC_INLINE bool base_setup(Tab& tb, Lds<W>& L, const int32_t* __restrict__ seqs, int B, int n, uint64_t tag,
+                            const WsArgs& ws, int blk, uint32_t epoch, WalkPlan& plan) {
   const bool cov = blk >= B;
   const int b = cov ? blk - B : blk;
   const int rec = cov ? ws.base_slots + b : b;
@@ -253,12 +246,12 @@ EPIC_INLINE void base_body(const DevTab& tb, Lds<W>& L, const int32_t* __restric
   if (L.sel_bad) {  // an illegal token: no snapshot, candidates report it themselves
     if (threadIdx.x == 0) h[4] = h[5] = 0;  // not reusable
     record_end(L, snap, 2, 0);
-    return;
+    return false;
   }
   int d = L.minp < nold ? L.minp : nold;
   if (owned && d == n && nold == n) {  // the record is this sequence's
     publish_record(L, snap, kRecDone | (uint32_t)h[1]);
-    return;
+    return false;
   }
   const int runs = owned ? h[1] : 0;
   const Snapshot* sp0 = reinterpret_cast<const Snapshot*>(snap + kSnapHeader);
@@ -269,7 +262,7 @@ EPIC_INLINE void base_body(const DevTab& tb, Lds<W>& L, const int32_t* __restric
   int i0 = 0;
   if (r0 >= 0) {
     i0 = sp0[r0].start;
-    resume_from_base<W>(L, ws, rec, r0, wk);  // the record's own chart up to run r0
+    resume_from_base<W>(tb, L, ws, rec, r0, wk);  // the record's own chart up to run r0
   }
   for (int k = threadIdx.x; k < n; k += NT) walked[k] = L.xtok[k];
   if (threadIdx.x == 0) {
@@ -278,18 +271,18 @@ EPIC_INLINE void base_body(const DevTab& tb, Lds<W>& L, const int32_t* __restric
     h[5] = (int32_t)(uint32_t)(tag >> 32);
   }
   publish_record(L, snap, (uint32_t)(r0 >= 0 ? r0 : 0));  // snapshots before r0 stay as they are
-  if (cov)
-    walk<W, true>(tb, L, wk, n, i0, r0 >= 0, snap, r0 >= 0 ? r0 : 0);
-  else
-    walk<W, false>(tb, L, wk, n, i0, r0 >= 0, snap, r0 >= 0 ? r0 : 0);
+  plan = WalkPlan{wk, cov, r0 >= 0, i0, r0 >= 0 ? r0 : 0, snap};
+  return true;
 }
 
 template <int W, int NT>
-__global__ void __launch_bounds__(NT) base_kernel(DevTab tb, const int32_t* __restrict__ seqs, int B, int n,
+__global__ void __launch_bounds__(NT) base_kernel(DevTab tab, const int32_t* __restrict__ seqs, int B, int n,
                                                   uint64_t tag, WsArgs ws) {
   __shared__ Lds<W> L;
+  Tab& tb = kernel_tab();
   stage_tables<W>(tb, L);
-  base_body<W, NT>(tb, L, seqs, B, n, tag, ws, blockIdx.x, 0u);
+  WalkPlan p;
+  if (base_setup<W, NT>(tb, L, seqs, B, n, tag, ws, blockIdx.x, 0u, p)) run_walk<W>(tb, L, p, n);
 }
 
 // Thread 0: wait until walk record `snap` holds the snapshot of masked run
@@ -311,125 +304,145 @@ __device__ inline uint64_t wait_record(const char* snap, uint32_t epoch, int run
 }
 
 // ------------------------------------------------------------------ validate
-// Candidate walks blk, blk + nblk, ... in walk slot blk.  With SHARE each
-// resumes from its sequence's base walk; with a nonzero epoch those base
-// walks run in the same launch and the walk first waits for its snapshot.
+// Prepare the walk of candidate c in walk slot `slot`.  With SHARE it resumes
+// from its sequence's base walk; with a nonzero epoch those base walks run in
+// the same launch and the walk first waits for its snapshot.  Returns 1 when
+// there is a walk to make, 0 when the verdict is known without one (left in
+// `r`), -1 when the candidate is malformed (its verdict is written here).
 template <int W, int NT, bool SHARE>
-EPIC_INLINE void validate_body(const DevTab& tb, Lds<W>& L, const int32_t* __restrict__ seqs, int B, int n,
+EPIC_INLINE int validate_setup(Tab& tb, Lds<W>& L, const int32_t* __restrict__ seqs, int B, int n,
                                const int32_t* __restrict__ cseq, const int32_t* __restrict__ cpos,
-                               const int32_t* __restrict__ ctok, int C, uint8_t* __restrict__ verdict,
-                               const WsArgs& ws, int blk, int nblk, uint32_t epoch) {
-  const WgWork wk = slot_work(ws, blk);
-  for (int c = blk; c < C; c += nblk) {
-    const int b = cseq[c], i = cpos[c], t = ctok[c];
-    const bool bad = b < 0 || b >= B || i < 0 || i >= n || t < 0 || t >= tb.V || seqs[(size_t)b * n + i] >= 0;
-    if (bad) {
-      if (threadIdx.x == 0) {
-        verdict[c] = 2;
-        atomicOr(tb.dev_err, (uint32_t)EPIC_DEV_BAD_CANDIDATE);
-      }
-      continue;
-    }
-    if (threadIdx.x == 0) L.sel_bad = 0;
-    __syncthreads();
-    for (int k = threadIdx.x; k < n; k += (int)blockDim.x) {
-      const int x = k == i ? t : seqs[(size_t)b * n + k];
-      if (x < -1 || x >= tb.V) L.sel_bad = 1;
-      L.xtok[k] = x;
-    }
-    __syncthreads();
-    if (L.sel_bad) {  // a token of the sequence is out of range
-      if (threadIdx.x == 0) {
-        verdict[c] = 2;
-        atomicOr(tb.dev_err, (uint32_t)EPIC_DEV_BAD_CANDIDATE);
-      }
-      __syncthreads();
-      continue;
-    }
-    int r;
-    if (SHARE) {
-      // the masked run of x_b holding position i: its start p0 and ordinal
-      if (threadIdx.x == 0) {
-        L.minp = -1;  // last fixed position before i
-        L.rep_b = 0;  // masked runs starting before p0
-      }
-      __syncthreads();
-      for (int k = threadIdx.x; k < i; k += NT)
-        if (L.xtok[k] >= 0) atomicMax(&L.minp, k);
-      __syncthreads();
-      const int p0 = L.minp + 1;
-      for (int k = threadIdx.x; k < p0; k += NT)
-        if (L.xtok[k] < 0 && (k == 0 || L.xtok[k - 1] >= 0)) atomicAdd(&L.rep_b, 1);
-      __syncthreads();
-      const int run = L.rep_b;
-      const int32_t* h = reinterpret_cast<const int32_t*>(snap_record(ws, b));
-      int ready = 1;  // 1: the record is final; 2: snapshot `run` is written; 0: not waited for in time
-      if (epoch) {
-        __syncthreads();
-        if (threadIdx.x == 0) {
-          const uint64_t v = wait_record(snap_record(ws, b), epoch, run);
-          L.result = v == 0 ? 0 : (((uint32_t)v & kRecDone) ? 1 : 2);
-        }
-        __syncthreads();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        ready = L.result;
-      }
-      const int status = ready == 1 ? h[0] : 0, runs = ready == 1 ? h[1] : run + 1;
-      if (ready == 0) {
-        r = walk<W, false>(tb, L, wk, n);
-      } else if (run < runs) {
-        WgWork wr = wk;
-        resume_from_base<W>(L, ws, b, run, wr);
-        r = walk<W, false>(tb, L, wr, n, p0, true);
-      } else {
-        r = status == 1 ? 0 : -1;  // the shared prefix died, or overflowed
-        if (threadIdx.x == 0 && r < 0) L.overflow = kOvEntries;
-      }
-    } else {
-      r = walk<W, false>(tb, L, wk, n);
-    }
+                               const int32_t* __restrict__ ctok, int c, uint8_t* __restrict__ verdict,
+                               const WsArgs& ws, int slot, uint32_t epoch, WalkPlan& plan, int& r) {
+  const int b = cseq[c], i = cpos[c], t = ctok[c];
+  const bool bad = b < 0 || b >= B || i < 0 || i >= n || t < 0 || t >= tb.V || seqs[(size_t)b * n + i] >= 0;
+  if (bad) {
     if (threadIdx.x == 0) {
-      verdict[c] = (uint8_t)(r < 0 ? 2 : r);
-      if (r < 0) atomicOr(tb.dev_err, (uint32_t)EPIC_DEV_CAPACITY | (1u << (8 + (L.overflow & 15))));
+      verdict[c] = 2;
+      atomicOr(tb.dev_err, (uint32_t)EPIC_DEV_BAD_CANDIDATE);
+    }
+    return -1;
+  }
+  if (threadIdx.x == 0) L.sel_bad = 0;
+  __syncthreads();
+  for (int k = threadIdx.x; k < n; k += (int)blockDim.x) {
+    const int x = k == i ? t : seqs[(size_t)b * n + k];
+    if (x < -1 || x >= tb.V) L.sel_bad = 1;
+    L.xtok[k] = x;
+  }
+  __syncthreads();
+  if (L.sel_bad) {  // a token of the sequence is out of range
+    if (threadIdx.x == 0) {
+      verdict[c] = 2;
+      atomicOr(tb.dev_err, (uint32_t)EPIC_DEV_BAD_CANDIDATE);
     }
     __syncthreads();
+    return -1;
   }
+  plan = WalkPlan{slot_work(ws, slot), false, false, 0, 0, nullptr};
+  if constexpr (SHARE) {
+    // the masked run of x_b holding position i: its start p0 and ordinal
+    if (threadIdx.x == 0) {
+      L.minp = -1;  // last fixed position before i
+      L.rep_b = 0;  // masked runs starting before p0
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < i; k += NT)
+      if (L.xtok[k] >= 0) atomicMax(&L.minp, k);
+    __syncthreads();
+    const int p0 = L.minp + 1;
+    for (int k = threadIdx.x; k < p0; k += NT)
+      if (L.xtok[k] < 0 && (k == 0 || L.xtok[k - 1] >= 0)) atomicAdd(&L.rep_b, 1);
+    __syncthreads();
+    const int run = L.rep_b;
+    const int32_t* h = reinterpret_cast<const int32_t*>(snap_record(ws, b));
+    int ready = 1;  // 1: the record is final; 2: snapshot `run` is written; 0: not waited for in time
+    if (epoch) {
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        const uint64_t v = wait_record(snap_record(ws, b), epoch, run);
+        L.result = v == 0 ? 0 : (((uint32_t)v & kRecDone) ? 1 : 2);
+      }
+      __syncthreads();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      ready = L.result;
+    }
+    const int status = ready == 1 ? h[0] : 0, runs = ready == 1 ? h[1] : run + 1;
+    if (ready != 0 && run >= runs) {
+      r = status == 1 ? 0 : -1;  // the shared prefix died, or overflowed
+      if (threadIdx.x == 0 && r < 0) L.overflow = kOvEntries;
+      return 0;
+    }
+    if (ready != 0) {
+      resume_from_base<W>(tb, L, ws, b, run, plan.wk);
+      plan.resume = true;
+      plan.i0 = p0;
+    }
+  }
+  return 1;
 }
 
-template <int W, int NT, bool SHARE>
-__global__ void __launch_bounds__(NT) validate_kernel(DevTab tb, const int32_t* __restrict__ seqs, int B,
-                                                            int n, const int32_t* __restrict__ cseq,
-                                                            const int32_t* __restrict__ cpos,
-                                                            const int32_t* __restrict__ ctok, int C,
-                                                            uint8_t* __restrict__ verdict, WsArgs ws) {
+// Candidate c's verdict from the outcome of its walk.
+template <int W>
+EPIC_INLINE void write_verdict(Tab& tb, const Lds<W>& L, uint8_t* __restrict__ verdict, int c, int r) {
+  if (threadIdx.x == 0) {
+    verdict[c] = (uint8_t)(r < 0 ? 2 : r);
+    if (r < 0) atomicOr(tb.dev_err, (uint32_t)EPIC_DEV_CAPACITY | (1u << (8 + (L.overflow & 15))));
+  }
+  __syncthreads();
+}
+
+// Candidate walks blockIdx.x, + gridDim.x, ... in walk slot blockIdx.x, each
+// from the first token.
+template <int W, int NT>
+__global__ void __launch_bounds__(NT) validate_kernel(DevTab tab, const int32_t* __restrict__ seqs, int B, int n,
+                                                      const int32_t* __restrict__ cseq,
+                                                      const int32_t* __restrict__ cpos,
+                                                      const int32_t* __restrict__ ctok, int C,
+                                                      uint8_t* __restrict__ verdict, WsArgs ws) {
   __shared__ Lds<W> L;
+  Tab& tb = kernel_tab();
   stage_tables<W>(tb, L);
-  validate_body<W, NT, SHARE>(tb, L, seqs, B, n, cseq, cpos, ctok, C, verdict, ws, blockIdx.x, gridDim.x, 0u);
+  for (int c = blockIdx.x; c < C; c += (int)gridDim.x) {
+    WalkPlan p;
+    int r = 0;
+    if (validate_setup<W, NT, false>(tb, L, seqs, B, n, cseq, cpos, ctok, c, verdict, ws, blockIdx.x, 0u, p, r) < 0)
+      continue;
+    write_verdict<W>(tb, L, verdict, c, run_walk<W>(tb, L, p, n));
+  }
 }
 
 // Base walks and the candidate walks that resume from them in one launch:
 // workgroups 0 .. gb-1 are the base walks (as base_kernel), the others the
-// candidate walks (as validate_kernel), each of which waits until the base
+// candidate walks, each of which waits until the base
 // walk of its sequence has written the snapshot it resumes from, so that
 // candidate walks overlap the rest of the base walks.  Base walks have the
 // lowest workgroup numbers and wait on nothing, so they are dispatched first
 // and finish; a candidate walk that is not released in time walks from the
 // start instead.  The base walks' work counts apart (base_work).
 template <int W, int NT>
-__global__ void __launch_bounds__(NT) base_validate_kernel(DevTab tb, const int32_t* __restrict__ seqs, int B, int n,
+__global__ void __launch_bounds__(NT) base_validate_kernel(DevTab tab, const int32_t* __restrict__ seqs, int B, int n,
                                                            uint64_t tag, int gb, const int32_t* __restrict__ cseq,
                                                            const int32_t* __restrict__ cpos,
                                                            const int32_t* __restrict__ ctok, int C,
                                                            uint8_t* __restrict__ verdict, WsArgs ws, uint32_t epoch,
                                                            unsigned long long* base_work) {
   __shared__ Lds<W> L;
+  Tab& tb = kernel_tab();
   stage_tables<W>(tb, L);
-  if ((int)blockIdx.x < gb) {
-    if (threadIdx.x == 0) L.work_to = base_work;
-    base_body<W, NT>(tb, L, seqs, B, n, tag, ws, blockIdx.x, epoch);
-  } else {
-    validate_body<W, NT, true>(tb, L, seqs, B, n, cseq, cpos, ctok, C, verdict, ws, blockIdx.x - gb,
-                               gridDim.x - gb, epoch);
+  const bool base = (int)blockIdx.x < gb;
+  if (base && threadIdx.x == 0) L.work_to = base_work;
+  const int slot = (int)blockIdx.x - gb, nblk = (int)gridDim.x - gb;
+  for (int c = base ? 0 : slot; base || c < C; c += nblk) {
+    WalkPlan p;
+    int r = 0, go;
+    if (base)
+      go = base_setup<W, NT>(tb, L, seqs, B, n, tag, ws, blockIdx.x, epoch, p) ? 1 : -1;
+    else
+      go = validate_setup<W, NT, true>(tb, L, seqs, B, n, cseq, cpos, ctok, c, verdict, ws, slot, epoch, p, r);
+    if (go > 0) r = run_walk<W>(tb, L, p, n);
+    if (base) return;
+    if (go >= 0) write_verdict<W>(tb, L, verdict, c, r);
   }
 }
 
@@ -609,7 +622,7 @@ __host__ __device__ inline bool alg4_replay(Alg4& a, int m, uint64_t path, int d
 // 0 ok, 1 repeated position or NaN confidence, 2 more than 64 candidates,
 // 3 a verdict-1 candidate or a sequence token that is not legal.
 template <int W>
-EPIC_DEV int select_setup(const DevTab& tb, Lds<W>& L, const int32_t* __restrict__ seqs, int n,
+EPIC_DEV int select_setup(Tab& tb, Lds<W>& L, const int32_t* __restrict__ seqs, int n,
                             const int32_t* __restrict__ cseq, const int32_t* __restrict__ cpos,
                             const int32_t* __restrict__ ctok, const float* __restrict__ conf,
                             const uint8_t* __restrict__ verdict, int C, int b, uint8_t* __restrict__ selected) {
@@ -691,20 +704,16 @@ EPIC_DEV void select_apply(Lds<W>& L, const int32_t* __restrict__ seqs, int n, i
 }
 
 // One check of Alg. 4 for sequence b: the walk of x_b with the sorted
-// candidates in msk applied (relaxed: cover graph; exact: Earley graph).
-// With `share`, the walk resumes from the sequence's base walk at the masked
-// run holding the subset's lowest position: x_b and x_b + S agree before it.
-template <int W, bool COVER, bool SHARE>
-EPIC_INLINE int select_walk_body(const DevTab& tb, Lds<W>& L, const WgWork& wk, const WsArgs& ws,
-                           const int32_t* __restrict__ seqs, int n, int b, uint64_t msk) {
+// candidates in msk applied (relaxed: cover graph; exact: Earley graph), in
+// walk slot blockIdx.x.  With SHARE, the walk resumes from the sequence's base
+// walk at the masked run holding the subset's lowest position: x_b and x_b + S
+// agree before it.
+template <int W, bool SHARE>
+EPIC_INLINE int select_walk(Tab& tb, Lds<W>& L, const WsArgs& ws, const int32_t* __restrict__ seqs, int n, int b,
+                            uint64_t msk, bool cover) {
   select_apply<W>(L, seqs, n, b, msk);
-  if constexpr (!SHARE) {
-    return walk<W, COVER>(tb, L, wk, n);
-  } else {
-  WgWork wr = wk;
-  int p0 = 0;
-  bool resume = false;
-  {
+  WalkPlan p{slot_work(ws, blockIdx.x), cover, false, 0, 0, nullptr};
+  if constexpr (SHARE) {
     if (threadIdx.x == 0) {
       int pmin = n;
       for (int i = 0; i < L.sel_n; ++i)
@@ -718,11 +727,11 @@ EPIC_INLINE int select_walk_body(const DevTab& tb, Lds<W>& L, const WgWork& wk, 
     for (int k = threadIdx.x; k < pmin; k += blockDim.x)
       if (L.xtok[k] >= 0) atomicMax(&L.minp, k);
     __syncthreads();
-    p0 = L.minp + 1;
+    const int p0 = L.minp + 1;
     for (int k = threadIdx.x; k < p0; k += blockDim.x)
       if (L.xtok[k] < 0 && (k == 0 || L.xtok[k - 1] >= 0)) atomicAdd(&L.rep_b, 1);
     __syncthreads();
-    const int run = L.rep_b, rec = COVER ? ws.base_slots + b : b;
+    const int run = L.rep_b, rec = cover ? ws.base_slots + b : b;
     const int32_t* h = reinterpret_cast<const int32_t*>(snap_record(ws, rec));
     const int status = h[0], runs = h[1];
     if (run >= runs) {
@@ -731,40 +740,11 @@ EPIC_INLINE int select_walk_body(const DevTab& tb, Lds<W>& L, const WgWork& wk, 
       __syncthreads();
       return -1;
     }
-    resume_from_base<W>(L, ws, rec, run, wr);
-    resume = true;
+    resume_from_base<W>(tb, L, ws, rec, run, p.wk);
+    p.resume = true;
+    p.i0 = p0;
   }
-  return walk<W, COVER>(tb, L, wr, n, resume ? p0 : 0, resume);
-  }
-}
-
-// A check walk kept as a function of its own for 16-word item sets in the
-// selection.  It measured faster than the inlined walk although its call
-// frame costs more per-lane scratch: at 1024 threads per workgroup (128
-// registers per lane), where the inlined walk spills in its inner loops,
-// 29.7 against 31.7 ms of C-like selection per 256-token step; at 512
-// threads, on checks resumed from base walks, 4.12 against 4.44 ms per
-// 1024-token step.  Narrower item sets, and the sequential fallback, inline
-// it.
-// It takes the walk slot's index, not its descriptor: a descriptor passed by
-// reference would live in per-lane scratch, and the walk would read its
-// pointers from there.
-template <int W, bool COVER, bool SHARE>
-__device__ __attribute__((noinline)) int select_walk_call(const DevTab& tb, Lds<W>& L, int slot, const WsArgs& ws,
-                                                          const int32_t* __restrict__ seqs, int n, int b,
-                                                          uint64_t msk) {
-  const WgWork wk = slot_work(ws, slot);
-  return select_walk_body<W, COVER, SHARE>(tb, L, wk, ws, seqs, n, b, msk);
-}
-
-// `wk` is the workgroup's own walk slot (slot_work(ws, blockIdx.x)).
-template <int W, bool COVER, bool SHARE, bool CALL = (W >= 16)>
-EPIC_INLINE int select_walk(const DevTab& tb, Lds<W>& L, const WgWork& wk, const WsArgs& ws,
-                                  const int32_t* __restrict__ seqs, int n, int b, uint64_t msk) {
-  if constexpr (CALL)
-    return select_walk_call<W, COVER, SHARE>(tb, L, (int)blockIdx.x, ws, seqs, n, b, msk);
-  else
-    return select_walk_body<W, COVER, SHARE>(tb, L, wk, ws, seqs, n, b, msk);
+  return run_walk<W>(tb, L, p, n);
 }
 
 // Speculated checks.  The machine's next check depends only on the number m
@@ -846,7 +826,7 @@ __global__ void spec_account_kernel(const int32_t* __restrict__ spec, int B, uns
 }
 
 template <int W, int NT, bool SHARE>
-__global__ void __launch_bounds__(NT) select_kernel(DevTab tb, const int32_t* __restrict__ seqs, int B, int n,
+__global__ void __launch_bounds__(NT) select_kernel(DevTab tab, const int32_t* __restrict__ seqs, int B, int n,
                                                           const int32_t* __restrict__ cseq,
                                                           const int32_t* __restrict__ cpos,
                                                           const int32_t* __restrict__ ctok,
@@ -859,7 +839,7 @@ __global__ void __launch_bounds__(NT) select_kernel(DevTab tb, const int32_t* __
   __shared__ uint64_t done_msk[kDoneChecks];
   __shared__ int done_val[kDoneChecks];  // result | (cover ? 2 : 0)
   __shared__ int done_n, done_hit, spec_pick, plan_j, implied;
-  const WgWork wk = slot_work(ws, blockIdx.x);
+  Tab& tb = kernel_tab();
   stage_tables<W>(tb, L);
   int32_t* spec_state = spec;             // [B * kPlan]
   int32_t* spec_used = spec + B * kPlan;  // [B * kPlan]: the selection took the result
@@ -1023,8 +1003,7 @@ __global__ void __launch_bounds__(NT) select_kernel(DevTab tb, const int32_t* __
     }
     const bool fresh = done_hit < 0;
     if (r < 0)
-      r = req == kReqCover ? select_walk<W, true, SHARE>(tb, L, wk, ws, seqs, n, b, msk)
-                           : select_walk<W, false, SHARE>(tb, L, wk, ws, seqs, n, b, msk);
+      r = select_walk<W, SHARE>(tb, L, ws, seqs, n, b, msk, req == kReqCover);
     if (helper) {
       if (threadIdx.x == 0) {
         // capacity (r < 0): the selection walks the check again and reports it
@@ -1082,7 +1061,7 @@ __global__ void __launch_bounds__(NT) select_kernel(DevTab tb, const int32_t* __
 // hi takes the hi-th (j, sequence) pair, j-th remaining candidate first;
 // results go to state words as the selection's (4 + outcome when done).
 template <int W, int NT, bool SHARE>
-__global__ void __launch_bounds__(NT) fallback_kernel(DevTab tb, const int32_t* __restrict__ seqs, int B, int n,
+__global__ void __launch_bounds__(NT) fallback_kernel(DevTab tab, const int32_t* __restrict__ seqs, int B, int n,
                                                       const int32_t* __restrict__ cseq,
                                                       const int32_t* __restrict__ cpos,
                                                       const int32_t* __restrict__ ctok,
@@ -1095,10 +1074,11 @@ __global__ void __launch_bounds__(NT) fallback_kernel(DevTab tb, const int32_t* 
   __shared__ Lds<W> L;
   __shared__ uint64_t kept;  // sorted candidates committed: B, then the accepted ones
   __shared__ int need, pick, decided;
-  const WgWork wk = slot_work(ws, blockIdx.x);
+  Tab& tb = kernel_tab();
   stage_tables<W>(tb, L);
-  const bool helpers = (int)gridDim.x > nprim;
-  if ((int)blockIdx.x >= nprim) {
+  const bool helpers = (int)gridDim.x > nprim, helper = (int)blockIdx.x >= nprim;
+  int hb = 0;
+  if (helper) {
     // remaining (valid, not selected) candidates per sequence, then the
     // hi-th pair over the (j, sequence) cells; the origin hash is free
     // until the walk, which clears it
@@ -1147,19 +1127,15 @@ __global__ void __launch_bounds__(NT) fallback_kernel(DevTab tb, const int32_t* 
         __hip_atomic_store(&spec[b * kPlan + pick], kSpecRunning, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    const int i = pick;
-    if (i < 0) return;
-    const int r = select_walk<W, false, SHARE, false>(tb, L, wk, ws, seqs, n, b, kept | (1ull << i));
-    if (threadIdx.x == 0)
-      __hip_atomic_store(&spec[b * kPlan + i], kSpecDone + (r < 0 ? 2 : r), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-    return;
+    if (pick < 0) return;
+    hb = b;
   }
-  for (int b = blockIdx.x; b < B; b += nprim) {
+  // (a helper's one check goes through the same call as the loop's)
+  for (int b = helper ? hb : (int)blockIdx.x; b < B; b += nprim) {
     // sorts b's verdict-1 candidates and clears accepted[] of all of b's
-    select_setup<W>(tb, L, seqs, n, cseq, cpos, ctok, conf, verdict, C, b, accepted);
+    if (!helper) select_setup<W>(tb, L, seqs, n, cseq, cpos, ctok, conf, verdict, C, b, accepted);
     uint64_t k0 = 0;  // B
-    if (threadIdx.x == 0) {
+    if (!helper && threadIdx.x == 0) {
       if (L.sel_bad)
         atomicOr(tb.dev_err, L.sel_bad == 2   ? (uint32_t)EPIC_DEV_CAPACITY
                              : L.sel_bad == 3 ? (uint32_t)EPIC_DEV_BAD_CANDIDATE
@@ -1173,10 +1149,10 @@ __global__ void __launch_bounds__(NT) fallback_kernel(DevTab tb, const int32_t* 
     __syncthreads();
     k0 = kept;
     if (!L.sel_bad) {
-      for (int i = 0; i < L.sel_n && need > 0; ++i) {
+      for (int i = helper ? pick : 0; helper || (i < L.sel_n && need > 0); ++i) {
         if ((kept >> i) & 1) continue;
         int r = -1;
-        if (helpers) {
+        if (helpers && !helper) {
           // a helper's check of x + B + c_i: a failure decides; a pass decides
           // while nothing beyond B is committed (then it is this check, and
           // a running one is waited for)
@@ -1195,7 +1171,13 @@ __global__ void __launch_bounds__(NT) fallback_kernel(DevTab tb, const int32_t* 
           __syncthreads();
           r = decided;
         }
-        if (r < 0) r = select_walk<W, false, SHARE, false>(tb, L, wk, ws, seqs, n, b, kept | (1ull << i));
+        if (r < 0) r = select_walk<W, SHARE>(tb, L, ws, seqs, n, b, kept | (1ull << i), false);
+        if (helper) {
+          if (threadIdx.x == 0)
+            __hip_atomic_store(&spec[b * kPlan + i], kSpecDone + (r < 0 ? 2 : r), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+          return;
+        }
         if (r < 0) {
           if (threadIdx.x == 0)
             atomicOr(tb.dev_err, (uint32_t)EPIC_DEV_CAPACITY | (1u << (8 + (L.overflow & 15))));
@@ -1345,8 +1327,8 @@ epic_status upload(epic_ctx* c) {
          o_flush = place(blob, H.flushlab), o_cexit = place(blob, H.cls_exit), o_cint = place(blob, H.cls_internal),
          o_centry = place(blob, H.cls_entry), o_cflush = place(blob, H.cls_flush), o_expt = place(blob, H.exp_t),
          o_comp = place(blob, H.complete), o_nsym = place(blob, H.next_sym), o_mn = place(blob, H.mn),
-         o_gtm = place(blob, H.gap_tm), o_gown = place(blob, H.gap_own), o_ccl = place(blob, H.cover_cl),
-         o_enib = place(blob, H.expn_nib), o_pnib = place(blob, H.pred_nib), o_gcov = place(blob, H.gap_cover),
+         o_gtm = place(blob, H.gap_tm), o_gown = place(blob, H.gap_own), o_cnt = place(blob, H.cov_nt),
+         o_enib = place(blob, H.expn_nib), o_pnib = place(blob, H.pred_nib), o_gcnt = place(blob, H.gcov_nt), o_gtt = place(blob, H.gap_tt),
          o_lnib = place(blob, H.lhs_nib), o_pnnib = place(blob, H.prednt_nib), o_cas1 = place(blob, H.cas1),
          o_cas = place(blob, H.cas), o_plan = place(blob, speculation_plan()),
          o_vb = place(blob, H.vbytes), o_vo = place(blob, H.voffs), o_endof = place(blob, H.end_of),
@@ -1408,14 +1390,15 @@ epic_status upload(epic_ctx* c) {
   t.gap_eps = H.gap_eps;
   t.expn_nib = (const uint32_t*)(d + o_enib);
   t.pred_nib = (const uint32_t*)(d + o_pnib);
-  t.gap_cover = (const uint32_t*)(d + o_gcov);
+  t.gcov_nt = (const uint32_t*)(d + o_gcnt);
+  t.gap_tt = (const uint32_t*)(d + o_gtt);
   t.lhs_nib = (const uint64_t*)(d + o_lnib);
   t.prednt_nib = (const uint64_t*)(d + o_pnnib);
   t.cas1 = (const uint64_t*)(d + o_cas1);
   t.cas = (const uint64_t*)(d + o_cas);
   t.gap_own_any = H.gap_own_any;
   t.plan = (const int32_t*)(d + o_plan);
-  t.cover_cl = (const uint32_t*)(d + o_ccl);
+  t.cov_nt = (const uint32_t*)(d + o_cnt);
   t.vbytes = (const uint8_t*)(d + o_vb);
   t.voffs = (const int32_t*)(d + o_vo);
   t.end_of = (const uint32_t*)(d + o_endof);
@@ -1424,6 +1407,13 @@ epic_status upload(epic_ctx* c) {
   t.wy_nt = (const int32_t*)(d + o_wynt);
   t.wy_own = (const int32_t*)(d + o_wyown);
   t.wy_pool = (const uint8_t*)(d + o_wypool);
+  t.off_cnt = (uint32_t)c->off_cnt;
+  t.off_org = (uint32_t)c->off_org;
+  t.off_pn = (uint32_t)c->off_pn;
+  t.off_bits = (uint32_t)c->off_bits;
+  t.off_cov = (uint32_t)c->off_cov;
+  t.maxn = c->maxn;
+  t.maxe = c->maxe;
   t.memo = c->d_memo;
   t.dev_err = c->d_err;
   t.work = (unsigned long long*)((char*)c->d_err + kWorkOff);
@@ -1434,13 +1424,6 @@ WsArgs ws_args(const epic_ctx* c, void* ws) {
   WsArgs a;
   a.base = (char*)ws;
   a.slot_bytes = c->slot_bytes;
-  a.off_cnt = c->off_cnt;
-  a.off_org = c->off_org;
-  a.off_pn = c->off_pn;
-  a.off_bits = c->off_bits;
-  a.off_cov = c->off_cov;
-  a.maxn = c->maxn;
-  a.maxe = c->maxe;
   a.nslot = c->nslot;
   a.base_slots = c->base_slots;
   a.max_seq = c->max_seq;
@@ -1598,11 +1581,11 @@ epic_status ValidateLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int 
   } else if (W >= 16 && grid <= c->num_cus) {
     KernelTimer kt(c, kKValidate, stream);
     if constexpr (W >= 16)
-      hipLaunchKernelGGL((validate_kernel<W, kThreadsWide, false>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
+      hipLaunchKernelGGL((validate_kernel<W, kThreadsWide>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
                          B, n, cs, cp, ct, C, verdict, wa);
   } else {
     KernelTimer kt(c, kKValidate, stream);
-    hipLaunchKernelGGL((validate_kernel<W, kThreads, false>), dim3(grid), dim3(kThreads), 0, stream, tb, seqs, B, n, cs,
+    hipLaunchKernelGGL((validate_kernel<W, kThreads>), dim3(grid), dim3(kThreads), 0, stream, tb, seqs, B, n, cs,
                        cp, ct, C, verdict, wa);
   }
   return hipGetLastError() == hipSuccess ? EPIC_OK : EPIC_ERR_HIP;
@@ -1632,12 +1615,6 @@ epic_status SelectLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int n,
   // for checks resumed from base walks (shorter walks, where 512 threads
   // measured faster: 4.12 against 4.25 ms per C-like 1024-token step)
   const bool wide = W >= 16 && grid <= c->num_cus && !share;
-  // The 1024-thread instance of the resumed-check selection is compiled but
-  // not launched: the out-of-line check walk that both instances call is then
-  // compiled to the 1024-thread register budget (128 per lane), and that code
-  // measured faster at 512 threads too (4.13 against 4.40 ms of C-like
-  // selection per 1024-token step) than a walk compiled for 512 threads only.
-  if constexpr (W >= 16) (void)&select_kernel<W, kThreadsWide, true>;
   const DevTab tb = tab_for(c, kKSelect);
   {
     KernelTimer kt(c, kKSelect, stream);
@@ -1703,10 +1680,10 @@ epic_status ValidatePlainLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B,
   const DevTab tb = tab_for(c, kKValidate);
   if (W >= 16 && grid <= c->num_cus) {
     if constexpr (W >= 16)
-      hipLaunchKernelGGL((validate_kernel<W, kThreadsWide, false>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
+      hipLaunchKernelGGL((validate_kernel<W, kThreadsWide>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
                          B, n, cs, cp, ct, C, verdict, wa);
   } else
-    hipLaunchKernelGGL((validate_kernel<W, kThreads, false>), dim3(grid), dim3(kThreads), 0, stream, tb, seqs, B, n, cs,
+    hipLaunchKernelGGL((validate_kernel<W, kThreads>), dim3(grid), dim3(kThreads), 0, stream, tb, seqs, B, n, cs,
                        cp, ct, C, verdict, wa);
   return hipGetLastError() == hipSuccess ? EPIC_OK : EPIC_ERR_HIP;
 }
@@ -1831,6 +1808,17 @@ epic_status epic_ctx_work_counters(epic_ctx* c, hipStream_t stream, int64_t* out
   }
   return EPIC_OK;
 }
+
+#ifdef EPIC_PROFILE
+// Profiling builds: read and clear the phase times of the walks (50 words).
+epic_status epic_diag_profile(epic_ctx* c, uint64_t* out) {
+  char* p = (char*)c->d_err + 64 * 8;
+  if (hipDeviceSynchronize() != hipSuccess || hipMemcpy(out, p, 400, hipMemcpyDeviceToHost) != hipSuccess ||
+      hipMemset(p, 0, 400) != hipSuccess)
+    return EPIC_ERR_HIP;
+  return EPIC_OK;
+}
+#endif
 
 epic_status epic_ctx_set_timing(epic_ctx* c, int32_t enable) {
   if (!c) return EPIC_ERR_NULL;

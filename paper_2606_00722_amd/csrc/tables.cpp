@@ -480,6 +480,20 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
       }
 
   // ---------------------------------------------------------------- cover
+  std::vector<uint32_t> cover_cl;  // epsilon closure of every cover state
+  // rows by nonterminal: out[((side*16 + i)*16 + v)*CW ..] = union of row(s)
+  // over the entry (side 0) or exit states s of the nonterminals 4i + b, b in v
+  auto nt_rows = [&](const uint32_t* row, uint32_t* out) {
+    for (int side = 0; side < 2; ++side)
+      for (int i = 0; i < 16; ++i)
+        for (int v = 0; v < 16; ++v)
+          for (int b = 0; b < 4; ++b) {
+            if (!((v >> b) & 1) || 4 * i + b >= N) continue;
+            const uint32_t* r = row + (size_t)(W * 32 + side * 64 + 4 * i + b) * H.CW;
+            for (int w = 0; w < H.CW; ++w) out[((size_t)(side * 16 + i) * 16 + v) * H.CW + w] |= r[w];
+          }
+  };
+  const size_t nt_words = (size_t)2 * 16 * 16 * H.CW;
   {
     // epsilon edges of the flattened recursive transition network (App. A.2):
     // entry_A -> (p,0) for A's productions, (p,|rhs|) -> exit_A, a nonterminal
@@ -500,7 +514,7 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
         }
       }
     }
-    H.cover_cl.assign((size_t)nbits * CW, 0);
+    cover_cl.assign((size_t)nbits * CW, 0);
     for (int s = 0; s < nbits; ++s) {
       std::vector<char> seen(nbits, 0);
       std::vector<int> st{s};
@@ -508,7 +522,7 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
       while (!st.empty()) {
         int u = st.back();
         st.pop_back();
-        set32(H.cover_cl, (size_t)s * CW, u);
+        set32(cover_cl, (size_t)s * CW, u);
         for (int v : eps[u])
           if (!seen[v]) {
             seen[v] = 1;
@@ -516,6 +530,8 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
           }
       }
     }
+    H.cov_nt.assign(nt_words, 0);
+    nt_rows(cover_cl.data(), H.cov_nt.data());
   }
 
   // ---------------------------------------------------------------- lexer
@@ -717,6 +733,7 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
   // is a label of an edge j -> k or a nonterminal derivable from j to k
   H.gap_eps = 0;
   H.gap_tm.assign((size_t)KK * KK * W, 0);
+  H.gap_tt.assign((size_t)KK * KK * W, 0);
   for (int j = 0; j < K; ++j)
     for (int k = 0; k < K; ++k) {
       if (epsp[(size_t)j * K + k]) H.gap_eps |= 1ull << (j * K + k);
@@ -724,7 +741,10 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
       uint64_t lab = H.cls_internal[(size_t)j * K + k] & ~(1ull << kLabelEps);
       for (int a = 0; a < T; ++a)
         if ((lab >> a) & 1)
-          for (int w = 0; w < W; ++w) m[w] |= H.exp_t[(size_t)a * W + w];
+          for (int w = 0; w < W; ++w) {
+            m[w] |= H.exp_t[(size_t)a * W + w];
+            H.gap_tt[((size_t)j * K + k) * W + w] |= H.exp_t[(size_t)a * W + w];
+          }
       for (int w = 0; w < W; ++w) H.gap_tm[((size_t)j * K + k) * W + w] = m[w];
     }
   H.gap_nt = gnt;
@@ -738,12 +758,12 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
     std::vector<std::vector<int>> ceps(S);
     for (int s = 0; s < S; ++s)
       for (int u = 0; u < S; ++u)
-        if (u != s && ((H.cover_cl[(size_t)s * CW + (u >> 5)] >> (u & 31)) & 1)) ceps[s].push_back(u);
-    H.gap_cover.assign((size_t)KK * KK * S * CW, 0);
+        if (u != s && ((cover_cl[(size_t)s * CW + (u >> 5)] >> (u & 31)) & 1)) ceps[s].push_back(u);
+    std::vector<uint32_t> gap_cover((size_t)KK * KK * S * CW, 0);
     std::vector<char> seen((size_t)KK * S);
     std::vector<int> stack;
     for (int j = 0; j < K; ++j)
-      for (int s0 = 0; s0 < S; ++s0) {
+      for (int s0 = W * 32; s0 < S; ++s0) {  // entry and exit states
         std::fill(seen.begin(), seen.end(), 0);
         stack.assign(1, j * S + s0);
         seen[(size_t)j * S + s0] = 1;
@@ -751,7 +771,7 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
           const int node = stack.back();
           stack.pop_back();
           const int c = node / S, st = node % S;
-          H.gap_cover[(((size_t)j * K + c) * S + s0) * CW + (st >> 5)] |= 1u << (st & 31);
+          gap_cover[(((size_t)j * K + c) * S + s0) * CW + (st >> 5)] |= 1u << (st & 31);
           auto push = [&](int c2, int s2) {
             if (!seen[(size_t)c2 * S + s2]) {
               seen[(size_t)c2 * S + s2] = 1;
@@ -766,6 +786,8 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
           }
         }
       }
+    H.gcov_nt.assign(KK * KK * nt_words, 0);
+    for (int jk = 0; jk < K * K; ++jk) nt_rows(&gap_cover[(size_t)jk * S * CW], &H.gcov_nt[jk * nt_words]);
   }
   H.gap_own.assign((size_t)KK * KK * W, 0);
   for (int j = 0; j < K; ++j) {

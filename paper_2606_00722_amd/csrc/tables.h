@@ -68,13 +68,15 @@ struct HostTables {
   std::vector<uint32_t> start_of;  // [N*W] items A -> . gamma
   std::vector<uint32_t> end_of;    // [N*W] items A -> gamma .
   // regular cover: state bit i < 32W is dotted item i (rule position), bit 32W+A is
-  // the entry state of nonterminal A, bit 32W+64+A its exit state; cover_cl[s] is
-  // the epsilon closure of state s (row of CW words, 32*CW rows)
-  std::vector<uint32_t> cover_cl;
-  // cover states reachable inside a masked run: gap_cover[((j*K + k)*32*CW + s)*CW ..]
-  // is the set of states at class node k reachable from state s at class node j
-  // (epsilon moves of the cover and the run's own labelled edges)
-  std::vector<uint32_t> gap_cover;
+  // the entry state of nonterminal A, bit 32W+64+A its exit state.
+  // cov_nt[((side*16 + i)*16 + v)*CW ..]: the epsilon closure of the entry
+  // (side 0) or exit (side 1) states of the nonterminals 4i + b with bit b of
+  // v set; gcov_nt[(((j*K + k)*2 + side)*16 + i)*16 + v)*CW ..]: the states at
+  // class node k of a masked run reachable from those at class node j (epsilon
+  // moves of the cover and the run's own labelled edges).
+  std::vector<uint32_t> cov_nt;
+  std::vector<uint32_t> gcov_nt;
+  std::vector<uint32_t> gap_tt;   // [K*K*W] items whose next symbol is a terminal label of a run's edge j -> k
   // witness extraction (failure recovery): terminal strings of what a masked
   // run derives between its class nodes.  A string in wy_pool is a 16-bit
   // length followed by that many terminal ids; offsets are -1 where there is
