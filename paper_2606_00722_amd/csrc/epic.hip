@@ -1112,10 +1112,11 @@ __global__ void __launch_bounds__(NT) fallback_kernel(DevTab tab, const int32_t*
     const int b = pick % B, j = pick / B;
     select_setup<W>(tb, L, seqs, n, cseq, cpos, ctok, conf, verdict, C, b, nullptr);
     if (threadIdx.x == 0) {
-      // the j-th remaining candidate in confidence order, and B
+      // the j-th remaining candidate in confidence order, and B (with more than
+      // 64 candidates only the first 64 indices are there: nothing is read)
       uint64_t k0 = 0;
       int i = -1, r = 0;
-      for (int q = 0; q < L.sel_n; ++q) {
+      for (int q = 0; !L.sel_bad && q < L.sel_n; ++q) {
         if (selected[L.sel_idx[q]])
           k0 |= 1ull << q;
         else if (r++ == j)
@@ -1141,7 +1142,7 @@ __global__ void __launch_bounds__(NT) fallback_kernel(DevTab tab, const int32_t*
                              : L.sel_bad == 3 ? (uint32_t)EPIC_DEV_BAD_CANDIDATE
                                               : (uint32_t)EPIC_DEV_BAD_SELECT);
       uint64_t k = 0;
-      for (int i = 0; i < L.sel_n; ++i)
+      for (int i = 0; !L.sel_bad && i < L.sel_n; ++i)
         if (selected[L.sel_idx[i]]) k |= 1ull << i;
       kept = k;
       need = num_commit[b] - __popcll(k);
