@@ -24,6 +24,7 @@
 #include <queue>
 #include <random>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/epic.h"
@@ -72,11 +73,15 @@ __device__ inline uint64_t grp_or64(uint64_t v) {
 
 #include "walker.inc"
 
-// Threads per walk: two wavefronts per SIMD (512 threads) hide part of the
-// memory latency of the chart reads.  Walks of 16-word item sets, whose rows
-// are the largest, run on 1024 threads when the launch has no more
-// workgroups than the device has CUs (each walk then owns its CU); measured
-// best on the C-like workloads of 256 and 1024 tokens.
+// Threads per walk.  A walk waits more than it computes, and its passes over
+// slots and chart entries are dealt to wavefronts, so 1024 threads (128
+// vector registers a lane) pay where rows are dense enough to feed them:
+// against 512 threads, JSON-like selection 1.26 -> 1.24 ms, SMILES-like
+// validation 2.86 -> 2.76 and selection 3.00 -> 2.83, arith the same, C-like
+// 48 x 128 validation 4.52 -> 4.13.  In block decoding (long sequences, a
+// few entries a row) 16-word walks are 8 % slower at 1024 (validation 1.75 ->
+// 1.89 ms): there the barriers of 16 wavefronts cost more than they share.
+// 8-word item sets, which no workload has, keep 512.
 constexpr int kThreads = 512;
 constexpr int kThreadsWide = 1024;
 constexpr int kDoneChecks = 64;  // answered checks remembered per sequence by the selection
@@ -1539,16 +1544,33 @@ struct WitnessLaunch {
 };
 
 #ifdef EPIC_KERNEL_UNIT
+// f(threads per walk, as a type) for sequences of n tokens (see kThreads).
+template <int W, class F>
+void with_threads(int n, F f) {
+  constexpr std::integral_constant<int, kThreadsWide> wide{};
+  constexpr std::integral_constant<int, kThreads> narrow{};
+  if constexpr (W <= 4) {
+    f(wide);
+  } else if constexpr (W >= 16) {
+    if (n < kShareSelectLen)
+      f(wide);
+    else
+      f(narrow);
+  } else {
+    f(narrow);
+  }
+}
+
 // Base walks of sequences 0..B-1 (gb = B: Earley graphs; 2B: also the cover
 // graphs).
 template <int W>
 void launch_base(epic_ctx* c, const int32_t* seqs, int B, int n, int gb, const WsArgs& wa, hipStream_t stream) {
   KernelTimer kt(c, kKBase, stream);
   const DevTab tb = tab_for(c, kKBase);
-  // 512 threads also for 16-word item sets: at 1024 (128 registers per
-  // lane) the walk spills and measured slower (C-like 1024-token base walks
-  // 1.13 against 1.10 ms)
-  hipLaunchKernelGGL((base_kernel<W, kThreads>), dim3(gb), dim3(kThreads), 0, stream, tb, seqs, B, n, c->tag, wa);
+  with_threads<W>(n, [&](auto nt) {
+    constexpr int NT = decltype(nt)::value;
+    hipLaunchKernelGGL((base_kernel<W, NT>), dim3(gb), dim3(NT), 0, stream, tb, seqs, B, n, c->tag, wa);
+  });
 }
 
 // Whether validation walks the base walks of both graphs and the selection's
@@ -1577,17 +1599,18 @@ epic_status ValidateLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int 
     const int gb = both ? 2 * B : B;
     if (++c->epoch == 0) ++c->epoch;  // 0 means "no waiting"
     KernelTimer kt(c, kKValidate, stream);
-    hipLaunchKernelGGL((base_validate_kernel<W, kThreads>), dim3(gb + grid), dim3(kThreads), 0, stream, tb, seqs, B,
-                       n, c->tag, gb, cs, cp, ct, C, verdict, wa, c->epoch, tab_for(c, kKBase).work);
-  } else if (W >= 16 && grid <= c->num_cus) {
-    KernelTimer kt(c, kKValidate, stream);
-    if constexpr (W >= 16)
-      hipLaunchKernelGGL((validate_kernel<W, kThreadsWide>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
-                         B, n, cs, cp, ct, C, verdict, wa);
+    with_threads<W>(n, [&](auto nt) {
+      constexpr int NT = decltype(nt)::value;
+      hipLaunchKernelGGL((base_validate_kernel<W, NT>), dim3(gb + grid), dim3(NT), 0, stream, tb, seqs, B, n, c->tag,
+                         gb, cs, cp, ct, C, verdict, wa, c->epoch, tab_for(c, kKBase).work);
+    });
   } else {
     KernelTimer kt(c, kKValidate, stream);
-    hipLaunchKernelGGL((validate_kernel<W, kThreads>), dim3(grid), dim3(kThreads), 0, stream, tb, seqs, B, n, cs,
-                       cp, ct, C, verdict, wa);
+    with_threads<W>(n, [&](auto nt) {
+      constexpr int NT = decltype(nt)::value;
+      hipLaunchKernelGGL((validate_kernel<W, NT>), dim3(grid), dim3(NT), 0, stream, tb, seqs, B, n, cs, cp, ct, C,
+                         verdict, wa);
+    });
   }
   return hipGetLastError() == hipSuccess ? EPIC_OK : EPIC_ERR_HIP;
 }
@@ -1612,23 +1635,18 @@ epic_status SelectLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int n,
     hipLaunchKernelGGL(spec_clear_kernel<W>, dim3((spec_words(B) + 255) / 256), dim3(256), 0, stream, spec,
                        spec_words(B));
   }
-  // 1024 threads for 16-word item sets when every workgroup has a CU, except
-  // for checks resumed from base walks (shorter walks, where 512 threads
-  // measured faster: 4.12 against 4.25 ms per C-like 1024-token step)
-  const bool wide = W >= 16 && grid <= c->num_cus && !share;
   const DevTab tb = tab_for(c, kKSelect);
   {
     KernelTimer kt(c, kKSelect, stream);
-    if (wide) {
-      if constexpr (W >= 16)
-        hipLaunchKernelGGL((select_kernel<W, kThreadsWide, false>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
-                           B, n, cs, cp, ct, conf, verdict, C, sel, (long long*)counts, spec, wa);
-    } else if (share)
-      hipLaunchKernelGGL((select_kernel<W, kThreads, true>), dim3(grid), dim3(kThreads), 0, stream, tb, seqs, B, n,
-                         cs, cp, ct, conf, verdict, C, sel, (long long*)counts, spec, wa);
-    else
-      hipLaunchKernelGGL((select_kernel<W, kThreads, false>), dim3(grid), dim3(kThreads), 0, stream, tb, seqs, B, n,
-                         cs, cp, ct, conf, verdict, C, sel, (long long*)counts, spec, wa);
+    with_threads<W>(n, [&](auto nt) {
+      constexpr int NT = decltype(nt)::value;
+      if (share)
+        hipLaunchKernelGGL((select_kernel<W, NT, true>), dim3(grid), dim3(NT), 0, stream, tb, seqs, B, n, cs, cp, ct,
+                           conf, verdict, C, sel, (long long*)counts, spec, wa);
+      else
+        hipLaunchKernelGGL((select_kernel<W, NT, false>), dim3(grid), dim3(NT), 0, stream, tb, seqs, B, n, cs, cp, ct,
+                           conf, verdict, C, sel, (long long*)counts, spec, wa);
+    });
   }
   if (grid > B) {
     KernelTimer kt(c, kKSpecClear, stream);
@@ -1659,14 +1677,16 @@ epic_status FallbackLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int 
     hipLaunchKernelGGL(spec_clear_kernel<W>, dim3((B * kPlan + 255) / 256), dim3(256), 0, stream, spec, B * kPlan);
   }
   KernelTimer kt(c, kKFallback, stream);
-  if (share)
-    hipLaunchKernelGGL((fallback_kernel<W, kThreads, true>), dim3(grid), dim3(kThreads), 0, stream,
-                       tab_for(c, kKFallback), seqs, B, n, cs, cp, ct, conf, verdict, sel, num_commit, C, accepted, wa,
-                       nprim, spec);
-  else
-    hipLaunchKernelGGL((fallback_kernel<W, kThreads, false>), dim3(grid), dim3(kThreads), 0, stream,
-                       tab_for(c, kKFallback), seqs, B, n, cs, cp, ct, conf, verdict, sel, num_commit, C, accepted, wa,
-                       nprim, spec);
+  with_threads<W>(n, [&](auto nt) {
+    constexpr int NT = decltype(nt)::value;
+    const DevTab tb = tab_for(c, kKFallback);
+    if (share)
+      hipLaunchKernelGGL((fallback_kernel<W, NT, true>), dim3(grid), dim3(NT), 0, stream, tb, seqs, B, n, cs, cp, ct,
+                         conf, verdict, sel, num_commit, C, accepted, wa, nprim, spec);
+    else
+      hipLaunchKernelGGL((fallback_kernel<W, NT, false>), dim3(grid), dim3(NT), 0, stream, tb, seqs, B, n, cs, cp, ct,
+                         conf, verdict, sel, num_commit, C, accepted, wa, nprim, spec);
+  });
   return hipGetLastError() == hipSuccess ? EPIC_OK : EPIC_ERR_HIP;
 }
 
@@ -1679,13 +1699,11 @@ epic_status ValidatePlainLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B,
   wa.base_slots = 0;
   const int grid = std::min(C, nslot);
   const DevTab tb = tab_for(c, kKValidate);
-  if (W >= 16 && grid <= c->num_cus) {
-    if constexpr (W >= 16)
-      hipLaunchKernelGGL((validate_kernel<W, kThreadsWide>), dim3(grid), dim3(kThreadsWide), 0, stream, tb, seqs,
-                         B, n, cs, cp, ct, C, verdict, wa);
-  } else
-    hipLaunchKernelGGL((validate_kernel<W, kThreads>), dim3(grid), dim3(kThreads), 0, stream, tb, seqs, B, n, cs,
-                       cp, ct, C, verdict, wa);
+  with_threads<W>(n, [&](auto nt) {
+    constexpr int NT = decltype(nt)::value;
+    hipLaunchKernelGGL((validate_kernel<W, NT>), dim3(grid), dim3(NT), 0, stream, tb, seqs, B, n, cs, cp, ct, C, verdict,
+                       wa);
+  });
   return hipGetLastError() == hipSuccess ? EPIC_OK : EPIC_ERR_HIP;
 }
 
