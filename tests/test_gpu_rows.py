@@ -1,0 +1,112 @@
+"""Chart rows at the edges of the walk's passes, on the device through the C
+ABI, against the oracle's verdicts and selections (whole numbers, so equal):
+rows with more entries than a wavefront takes at a time, more slots than
+wavefronts share out at once, many in-edges, runs of more tokens than one
+wavefront scans, and calls with more candidates than CUs, whose selection
+resumes from base walks."""
+import numpy as np
+import pytest
+
+from paper_2606_00722_amd import grammars as G
+from paper_2606_00722_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+NTH = 8
+
+
+@pytest.fixture(scope="module")
+def gpu_mod():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible to the gpu-marked tests")
+    from tests import gpu_util
+
+    return gpu_util
+
+
+def masked_case(preset, B, n, pattern, seed):
+    """Hidden answers of the preset with masks at a fixed pattern, proposals
+    at masked positions (the hidden token half of the time)."""
+    inst = W.make_instance(preset, seed, B=B, n=n)
+    x = inst.hidden.copy()
+    if pattern == "alternate":  # as many masked runs, and slots in their rows, as fit
+        x[:, 1::2] = W.MASK
+    elif pattern == "third":
+        x[:, ::3] = W.MASK
+    elif pattern == "long run":  # over 64 fixed tokens between two masked runs
+        x[:, :2] = W.MASK
+        x[:, -2:] = W.MASK
+    elif pattern == "one run":
+        x[:, n // 4:3 * n // 4] = W.MASK
+    return inst, x.astype(np.int32)
+
+
+def proposals(inst, x, props, rng):
+    seq, pos, tok = [], [], []
+    for b in range(x.shape[0]):
+        at = np.flatnonzero(x[b] == W.MASK)
+        p = rng.choice(at, min(props, len(at)), replace=False)
+        keep = rng.random(len(p)) < 0.5
+        seq.append(np.full(len(p), b))
+        pos.append(p)
+        tok.append(np.where(keep, inst.hidden[b, p], rng.integers(0, inst.vocab.size, len(p))))
+    seq, pos, tok = (np.concatenate(a).astype(np.int32) for a in (seq, pos, tok))
+    return seq, pos, tok, rng.random(len(seq), dtype=np.float32)
+
+
+@pytest.mark.parametrize("preset,B,n,pattern,props", [
+    (1, 3, 129, "alternate", 8),    # one word a set, 64 masked runs
+    (1, 2, 200, "long run", 4),     # a run of 196 tokens
+    (2, 2, 128, "alternate", 6),    # four words
+    (2, 2, 90, "long run", 4),
+    (3, 2, 97, "third", 6),         # one class node a run
+    (4, 2, 64, "alternate", 6),     # sixteen words
+    (4, 2, 96, "long run", 4),
+    (4, 2, 63, "one run", 6),
+    (2, 40, 32, "third", 8),        # 320 candidates, more than CUs: selection from base walks
+    (4, 24, 24, "third", 8),        # 192 candidates and 48 base walks: they fit on the CUs
+    (4, 33, 24, "third", 8),        # 264 candidates: more than CUs
+    (4, 31, 24, "third", 8),        # 248 candidates, but not with 62 base walks: no sharing
+])
+def test_rows_at_pass_edges(preset, B, n, pattern, props, gpu_mod, oracle_lib):
+    rng = np.random.default_rng([preset, B, n])
+    inst, x = masked_case(preset, B, n, pattern, 7)
+    seq, pos, tok, conf = proposals(inst, x, props, rng)
+    p = oracle_lib.problem_from(inst.lang, inst.vocab)
+    g = gpu_mod.Gpu(W.arrays(inst.lang, inst.vocab), B, n, len(seq))
+    want = oracle_lib.validate_batch(p, x, seq, pos, tok, NTH)
+    for _ in range(3):  # the order in which wavefronts add to a row differs from call to call
+        assert np.array_equal(g.validate(x, seq, pos, tok), want)
+    assert g.errors() == 0
+    want_s, counts, st = oracle_lib.select(p, x, seq, pos, tok, conf, want, NTH)
+    sel, got_counts = g.select(x, seq, pos, tok, conf, want)
+    assert st == 0 and g.errors() == 0
+    assert np.array_equal(sel, want_s) and tuple(got_counts) == tuple(int(c) for c in counts)
+
+
+@pytest.mark.parametrize("name", ["tiny_paren", "tiny_expr", "tiny_ab"])
+def test_long_rows_of_tiny_languages(name, gpu_mod, oracle_lib):
+    """Nullable productions and a three-class lexer (completion by iteration)
+    with every other token masked: verdicts of every masked position and token
+    equal the oracle's."""
+    from tests.util import custom_vocab
+
+    lang = G.language(name)
+    vocab = custom_vocab(lang, {"tiny_paren": ["((", "))", "()"], "tiny_expr": ["a+", "(a", " a"],
+                                "tiny_ab": ["ab", "ba", "cc"]}[name])
+    rng = np.random.default_rng(11)
+    n = 33
+    x = rng.integers(0, vocab.size, size=(6, n)).astype(np.int32)
+    x[:, ::2] = W.MASK
+    x[0, 1::4] = W.MASK
+    x[1] = W.MASK
+    at = np.argwhere(x == W.MASK)
+    at = at[rng.choice(len(at), 40, replace=False)]
+    seq, pos = at[:, 0].astype(np.int32), at[:, 1].astype(np.int32)
+    tok = rng.integers(0, vocab.size, size=len(at)).astype(np.int32)
+    p = oracle_lib.problem_from(lang, vocab)
+    g = gpu_mod.Gpu(W.arrays(lang, vocab), x.shape[0], n, len(at))
+    assert np.array_equal(g.validate(x, seq, pos, tok), oracle_lib.validate_batch(p, x, seq, pos, tok, NTH))
+    assert g.errors() == 0
