@@ -506,14 +506,13 @@ def main() -> int:
     fallback_ms = float(np.mean([a.elapsed_time(b) for a, b in fb_ms])) if fb_ms else None
 
     # algorithmic bytes of the walks of one kernel kind, from its work
-    # counters over the timed steps: chart entries written (4W B of items,
-    # 8 B expected nonterminals, 8 B expected terminals, 4 B origin), memo
-    # entries read (16 B), chart entries pulled by row tasks (origin, summary
-    # and items: 12 + 4W B), one sequence row per walk (4n B)
+    # counters over the timed steps: chart entries written (4W B of items, 4 B
+    # origin), memo entries read (16 B), chart entries pulled (items and
+    # origin), one sequence row per walk (4n B)
     Wd = ctx.item_words
 
     def walk_bytes(c):
-        return float(c[1] * (4 * Wd + 20) + c[2] * 16 + c[4] * (12 + 4 * Wd) + c[0] * 4 * inst.n)
+        return float(c[1] * (4 * Wd + 4) + c[2] * 16 + c[4] * (4 + 4 * Wd) + c[0] * 4 * inst.n)
 
     V, Q = ctx.vocab_size, ctx.num_states
     kern = {}
