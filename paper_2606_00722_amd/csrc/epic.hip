@@ -1574,16 +1574,34 @@ void launch_base(epic_ctx* c, const int32_t* seqs, int B, int n, int gb, const W
 }
 
 // Whether validation walks the base walks of both graphs and the selection's
-// checks resume from them: for long sequences, whenever those 2B walks fit
-// beside the candidate walks on the CUs (at the cost of walks then, JSON-like
-// 128-token steps 12.7K -> 13.3K checks/s, SMILES-like 256-token 9.85K ->
-// 10.2K), and when there are more candidate walks than CUs anyway, so that
-// validation resumes them from base walks too (JSON-like 128 x 128 step 6.48
-// -> 6.01 ms, C-like 48 x 128 11.24 -> 10.54).  In between, the base walks
-// would only make candidates wait for a CU (C-like 16 x 256: 12.6 -> 12.7 ms).
+// checks resume from them:
+//  * for long sequences;
+//  * when those 2B walks fit beside the candidate walks on the CUs (at the cost
+//    of walks then, JSON-like 128-token steps 12.7K -> 13.3K checks/s,
+//    SMILES-like 256-token 9.85K -> 10.2K);
+//  * when there are more candidate walks than CUs, so that validation resumes
+//    them from base walks too, and at least two candidates a sequence.  Alg. 4
+//    checks nothing for a sequence of one candidate: there the B cover walks,
+//    queued ahead of the candidates, only delay them (300 sequences of one
+//    candidate, validation + selection, on sequences that differ from the call
+//    before at their first token / as one decoding step from the next:
+//    JSON-like 128 tokens 3.58 / 2.66 ms without them, 4.98 / 3.08 with; C-like
+//    128 5.03 / 3.49 and 6.67 / 4.20; arith 32 0.89 / 0.65 and 1.32 / 0.83).
+//    From two on the selection gains what validation loses, most where a long
+//    fixed prefix is shared (150 sequences of two, without / with: C-like
+//    128-token blocks 2.41 / 1.87 ms, 300-token ones 4.72 / 2.69, JSON-like
+//    192-token blocks 2.89 / 1.97; uniform masks lose: JSON-like 128 4.90 /
+//    5.26, 64 tokens 90 % masked 0.93 / 1.09, SMILES-like 128 5.42 / 5.46).
+//    Over 16 such workloads of two candidates a sequence a step gains 1.12
+//    times (0.86 to 1.95), over 18 of four 1.17 times (0.94 to 2.2).  A caller
+//    that only validates pays for the cover walks: up to 14 % of its time from
+//    four candidates a sequence on.
+// In between, the base walks would only make candidates wait for a CU (C-like
+// 16 x 256: 12.6 -> 12.7 ms).
 static bool share_both(const epic_ctx* c, int B, int n, int C) {
   const int walks = std::min(C, c->nslot);
-  return B <= c->base_slots && (n >= kShareSelectLen || walks > c->num_cus || walks + 2 * B <= c->num_cus);
+  if (B > c->base_slots) return false;
+  return n >= kShareSelectLen || walks + 2 * B <= c->num_cus || (walks > c->num_cus && C >= 2 * B);
 }
 
 template <int W>

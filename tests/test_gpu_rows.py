@@ -86,6 +86,30 @@ def test_rows_at_pass_edges(preset, B, n, pattern, props, gpu_mod, oracle_lib):
     assert np.array_equal(sel, want_s) and tuple(got_counts) == tuple(int(c) for c in counts)
 
 
+@pytest.mark.parametrize("B,props,graphs", [
+    (300, 1, 1),  # one candidate a sequence: Alg. 4 makes no check, no cover walk is made for it
+    (129, 2, 2),  # 258 candidates, more than CUs: validation walks the cover graphs' base walks too
+    (128, 2, 0),  # 256: each has a CU, and base walks would not fit beside them
+])
+def test_base_walks_of_wide_calls(B, props, graphs, gpu_mod, oracle_lib):
+    """How many graphs of a sequence validation walks for prefix sharing."""
+    import torch
+
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the calls are sized for 256 CUs")
+    inst, x = masked_case(1, B, 12, "third", 5)
+    seq, pos, tok, conf = proposals(inst, x, props, np.random.default_rng(3))
+    assert len(seq) == B * props
+    p = oracle_lib.problem_from(inst.lang, inst.vocab)
+    g = gpu_mod.Gpu(W.arrays(inst.lang, inst.vocab), B, x.shape[1], len(seq))
+    want = oracle_lib.validate_batch(p, x, seq, pos, tok, NTH)
+    assert np.array_equal(g.validate(x, seq, pos, tok), want)
+    assert g.ctx.kernel_stats()["base"]["work"][0] == B * graphs
+    want_s, _, st = oracle_lib.select(p, x, seq, pos, tok, conf, want, NTH)
+    sel, _ = g.select(x, seq, pos, tok, conf, want)
+    assert st == 0 and g.errors() == 0 and np.array_equal(sel, want_s)
+
+
 @pytest.mark.parametrize("name", ["tiny_paren", "tiny_expr", "tiny_ab"])
 def test_long_rows_of_tiny_languages(name, gpu_mod, oracle_lib):
     """Nullable productions and a three-class lexer (completion by iteration)
