@@ -75,13 +75,25 @@ __device__ inline uint64_t grp_or64(uint64_t v) {
 
 // Threads per walk.  A walk waits more than it computes, and its passes over
 // slots and chart entries are dealt to wavefronts, so 1024 threads (128
-// vector registers a lane) pay where rows are dense enough to feed them:
-// against 512 threads, JSON-like selection 1.26 -> 1.24 ms, SMILES-like
-// validation 2.86 -> 2.76 and selection 3.00 -> 2.83, arith the same, C-like
-// 48 x 128 validation 4.52 -> 4.13.  In block decoding (long sequences, a
-// few entries a row) 16-word walks are 8 % slower at 1024 (validation 1.75 ->
-// 1.89 ms): there the barriers of 16 wavefronts cost more than they share.
-// 8-word item sets, which no workload has, keep 512.
+// vector registers a lane) pay where rows are dense enough to feed them, which
+// depends on the masks; the host knows only the length.
+//  * Item sets of up to four words: 1024.  Against 512, validation + selection
+//    of a step: SMILES-like 16 x 256 5.98 -> 5.72 ms, 4 x 512 18.8 -> 16.1,
+//    arith 4 x 512 13.3 -> 11.4, JSON-like 8 x 128 2.64 -> 2.60; sparse rows
+//    lose up to 4 % (JSON-like 64 x 128 10 % masked 2.21 -> 2.24, 64 x 64 90 %
+//    masked 1.49 -> 1.55, 16 x 512 blocks 3.06 -> 3.13).
+//  * 16 words, below 512 tokens: 1024.  Masks everywhere gain (C-like 16 x 128
+//    7.70 -> 7.38, 8 x 256 14.7 -> 13.2, 4 x 448 36.3 -> 29.6), 32-token blocks
+//    lose (16 x 128 2.99 -> 3.22, 64 x 256 3.85 -> 4.16, 24 x 448 6.00 -> 6.36).
+//  * 16 words, from 512 tokens on, with walks that resume from base walks: 512.
+//    Sequences of that length are decoded in blocks, where a walk is the few
+//    sparse rows behind the snapshot (24 x 640 3.50 ms against 3.71, 24 x 512
+//    3.44 against 3.68); masks everywhere would gain from 1024 (4 x 512 47.8
+//    against 37.5).
+//  * 16 words, validation without a workspace: 1024.  Every walk starts at the
+//    first token there, and blocks lose 1 to 3 % (12 x 640 16.5 -> 16.8 ms, 4 x
+//    1024 7.95 -> 8.16) where masks everywhere gain 20 % (4 x 512 44.5 -> 35.2).
+//  * 8 words, which no workload has: 512.
 constexpr int kThreads = 512;
 constexpr int kThreadsWide = 1024;
 constexpr int kDoneChecks = 64;  // answered checks remembered per sequence by the selection
@@ -1544,15 +1556,17 @@ struct WitnessLaunch {
 };
 
 #ifdef EPIC_KERNEL_UNIT
-// f(threads per walk, as a type) for sequences of n tokens (see kThreads).
+// f(threads per walk, as a type) for sequences of n tokens whose walks may
+// resume from base walks (shared) or all start at the first token (see
+// kThreads).
 template <int W, class F>
-void with_threads(int n, F f) {
+void with_threads(int n, bool shared, F f) {
   constexpr std::integral_constant<int, kThreadsWide> wide{};
   constexpr std::integral_constant<int, kThreads> narrow{};
   if constexpr (W <= 4) {
     f(wide);
   } else if constexpr (W >= 16) {
-    if (n < kShareSelectLen)
+    if (n < kShareSelectLen || !shared)
       f(wide);
     else
       f(narrow);
@@ -1567,7 +1581,7 @@ template <int W>
 void launch_base(epic_ctx* c, const int32_t* seqs, int B, int n, int gb, const WsArgs& wa, hipStream_t stream) {
   KernelTimer kt(c, kKBase, stream);
   const DevTab tb = tab_for(c, kKBase);
-  with_threads<W>(n, [&](auto nt) {
+  with_threads<W>(n, true, [&](auto nt) {
     constexpr int NT = decltype(nt)::value;
     hipLaunchKernelGGL((base_kernel<W, NT>), dim3(gb), dim3(NT), 0, stream, tb, seqs, B, n, c->tag, wa);
   });
@@ -1621,14 +1635,14 @@ epic_status ValidateLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int 
     const int gb = both ? 2 * B : B;
     if (++c->epoch == 0) ++c->epoch;  // 0 means "no waiting"
     KernelTimer kt(c, kKValidate, stream);
-    with_threads<W>(n, [&](auto nt) {
+    with_threads<W>(n, true, [&](auto nt) {
       constexpr int NT = decltype(nt)::value;
       hipLaunchKernelGGL((base_validate_kernel<W, NT>), dim3(gb + grid), dim3(NT), 0, stream, tb, seqs, B, n, c->tag,
                          gb, cs, cp, ct, C, verdict, wa, c->epoch, tab_for(c, kKBase).work);
     });
   } else {
     KernelTimer kt(c, kKValidate, stream);
-    with_threads<W>(n, [&](auto nt) {
+    with_threads<W>(n, true, [&](auto nt) {
       constexpr int NT = decltype(nt)::value;
       hipLaunchKernelGGL((validate_kernel<W, NT>), dim3(grid), dim3(NT), 0, stream, tb, seqs, B, n, cs, cp, ct, C,
                          verdict, wa);
@@ -1660,7 +1674,7 @@ epic_status SelectLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int n,
   const DevTab tb = tab_for(c, kKSelect);
   {
     KernelTimer kt(c, kKSelect, stream);
-    with_threads<W>(n, [&](auto nt) {
+    with_threads<W>(n, true, [&](auto nt) {
       constexpr int NT = decltype(nt)::value;
       if (share)
         hipLaunchKernelGGL((select_kernel<W, NT, true>), dim3(grid), dim3(NT), 0, stream, tb, seqs, B, n, cs, cp, ct,
@@ -1699,7 +1713,7 @@ epic_status FallbackLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int 
     hipLaunchKernelGGL(spec_clear_kernel<W>, dim3((B * kPlan + 255) / 256), dim3(256), 0, stream, spec, B * kPlan);
   }
   KernelTimer kt(c, kKFallback, stream);
-  with_threads<W>(n, [&](auto nt) {
+  with_threads<W>(n, true, [&](auto nt) {
     constexpr int NT = decltype(nt)::value;
     const DevTab tb = tab_for(c, kKFallback);
     if (share)
@@ -1721,7 +1735,7 @@ epic_status ValidatePlainLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B,
   wa.base_slots = 0;
   const int grid = std::min(C, nslot);
   const DevTab tb = tab_for(c, kKValidate);
-  with_threads<W>(n, [&](auto nt) {
+  with_threads<W>(n, false, [&](auto nt) {
     constexpr int NT = decltype(nt)::value;
     hipLaunchKernelGGL((validate_kernel<W, NT>), dim3(grid), dim3(NT), 0, stream, tb, seqs, B, n, cs, cp, ct, C, verdict,
                        wa);
