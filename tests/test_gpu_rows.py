@@ -2,12 +2,13 @@
 ABI, against the oracle's verdicts and selections (whole numbers, so equal):
 rows with more entries than a wavefront takes at a time, more slots than
 wavefronts share out at once, many in-edges, runs of more tokens than one
-wavefront scans, and calls with more candidates than CUs, whose selection
-resumes from base walks."""
+wavefront scans, calls with more candidates than CUs, whose selection resumes
+from base walks, and masked runs of one and of eight class nodes."""
 import numpy as np
 import pytest
 
 from paper_2606_00722_amd import grammars as G
+from paper_2606_00722_amd import lexspec as lx
 from paper_2606_00722_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -134,3 +135,90 @@ def test_long_rows_of_tiny_languages(name, gpu_mod, oracle_lib):
     g = gpu_mod.Gpu(W.arrays(lang, vocab), x.shape[0], n, len(at))
     assert np.array_equal(g.validate(x, seq, pos, tok), oracle_lib.validate_batch(p, x, seq, pos, tok, NTH))
     assert g.errors() == 0
+
+
+def test_one_gap_class_at_sixteen_words(gpu_mod, oracle_lib):
+    """The SMILES-like grammar, one class node a masked run, padded to sixteen
+    words a set."""
+    from tests.util import pad_language
+
+    inst, x = masked_case(3, 3, 50, "third", 9)
+    lang = pad_language(inst.lang)
+    seq, pos, tok, conf = proposals(inst, x, 8, np.random.default_rng(2))
+    p = oracle_lib.problem_from(lang, inst.vocab)
+    g = gpu_mod.Gpu(W.arrays(lang, inst.vocab), 3, 50, len(seq))
+    assert (g.ctx.gap_classes, g.ctx.item_words) == (1, 16)
+    want = oracle_lib.validate_batch(p, x, seq, pos, tok, NTH)
+    assert np.array_equal(g.validate(x, seq, pos, tok), want)
+    want_s, counts, st = oracle_lib.select(p, x, seq, pos, tok, conf, want, NTH)
+    sel, got_counts = g.select(x, seq, pos, tok, conf, want)
+    assert st == 0 and g.errors() == 0
+    assert np.array_equal(sel, want_s) and tuple(got_counts) == tuple(int(c) for c in counts)
+
+
+def pairs_language(only_z=False):
+    """Six pairs of letters x, y where x then y always lexes as xy, so that no
+    lexeme y follows a lexeme x: a lexer with eight gap classes.  Runs of z are
+    one lexeme, so that a lexeme can span any number of masked runs.  S is
+    right-recursive: a sequence of any lexemes, which completes at every origin
+    before when it completes, or z runs with a between them."""
+    firsts, seconds = "acegik", "bdfhjl"
+    pats = [w for x, y in zip(firsts, seconds) for w in (x, x + y, y)]
+    names = ["T%d" % i for i in range(len(pats))] + ["Z"]
+    prods = [("S", (t, "S")) for t in names] + [("S", (names[0],)), ("S", ("Z", "Z", "S"))]
+    if only_z:
+        prods = [("S", ("Z", names[0], "S")), ("S", ("Z",))]
+    g = G.Grammar(names, ["S"], prods, "S")
+    rules = [lx.LexerRule(n, lx.lit(w), g.tid[n]) for n, w in zip(names, pats)]
+    rules.append(lx.LexerRule("Z", lx.plus(lx.cls("z")), g.tid["Z"]))
+    return G.Language("pairs", g, rules, firsts + seconds + "z", {}, wordish=frozenset())
+
+
+def masked_runs(idx, runs, between, n, fill):
+    """`runs` masked tokens with the token `between` after each, then `fill`."""
+    x = np.full(n, idx[fill], np.int32)
+    x[0:2 * runs:2] = W.MASK
+    x[1:2 * runs:2] = idx[between]
+    return x
+
+
+@pytest.mark.parametrize("only_z,pad,words", [(False, 0, 4), (False, 2, 16), (True, 0, 1)])
+def test_many_gap_classes(only_z, pad, words, gpu_mod, oracle_lib):
+    """Eight class nodes a masked run: completion by iteration, at 4 and 16
+    words a set; and lexemes in progress over up to 18 masked runs, each of
+    which adds two, whose frontier entries enter the last runs by more than 256
+    label sets."""
+    from tests.util import custom_vocab, pad_language
+
+    lang = pairs_language(only_z)
+    vocab = custom_vocab(lang, ["ab", "zz", "ca"])
+    for _ in range(pad):
+        lang = pad_language(lang)
+    idx = {s: i for i, s in enumerate(vocab.strings)}
+    rng = np.random.default_rng(17)
+    n, runs = (38, 18) if only_z else (14, 5)
+    rows = [masked_runs(idx, runs, b"z", n, b"a"), masked_runs(idx, runs, b"z", n, b"zz"),
+            masked_runs(idx, 4, b"c", n, b"a")]
+    for _ in range(5):
+        x = np.full(n, idx[b"z"], np.int32) if only_z else rng.integers(0, vocab.size, n).astype(np.int32)
+        x[rng.choice(n, 6, replace=False)] = W.MASK
+        rows.append(x)
+    rows.append(np.full(n, W.MASK, np.int32))
+    x = np.stack(rows)
+    at = np.argwhere(x == W.MASK)
+    seq, pos = np.repeat(at, 3, axis=0).astype(np.int32).T
+    tok = rng.integers(0, vocab.size, size=len(seq)).astype(np.int32)
+    p = oracle_lib.problem_from(lang, vocab)
+    g = gpu_mod.Gpu(W.arrays(lang, vocab), len(x), n, len(seq))
+    assert (g.ctx.gap_classes, g.ctx.item_words) == (8, words)
+    want = oracle_lib.validate_batch(p, x, seq, pos, tok, NTH)
+    got = g.validate(x, seq, pos, tok)
+    assert g.errors() == 0
+    assert np.array_equal(got, want) and 0 < int(want.sum()) < len(want)
+    one = np.unique(at[:, 0] * n + at[:, 1], return_index=True)[1] * 3  # a candidate a position
+    s1, p1, t1 = seq[one], pos[one], tok[one]
+    conf = rng.random(len(one), dtype=np.float32)
+    want_s, counts, st = oracle_lib.select(p, x, s1, p1, t1, conf, want[one], NTH)
+    sel, got_counts = g.select(x, s1, p1, t1, conf, want[one])
+    assert st == 0 and g.errors() == 0
+    assert np.array_equal(sel, want_s) and tuple(got_counts) == tuple(int(c) for c in counts)
