@@ -3,7 +3,8 @@ ABI, against the oracle's verdicts and selections (whole numbers, so equal):
 rows with more entries than a wavefront takes at a time, more slots than
 wavefronts share out at once, many in-edges, runs of more tokens than one
 wavefront scans, calls with more candidates than CUs, whose selection resumes
-from base walks, and masked runs of one and of eight class nodes."""
+from base walks, masked runs of one and of eight class nodes, and buffers that
+overflow."""
 import numpy as np
 import pytest
 
@@ -222,3 +223,58 @@ def test_many_gap_classes(only_z, pad, words, gpu_mod, oracle_lib):
     sel, got_counts = g.select(x, s1, p1, t1, conf, want[one])
     assert st == 0 and g.errors() == 0
     assert np.array_equal(sel, want_s) and tuple(got_counts) == tuple(int(c) for c in counts)
+
+
+# the error word's bits for the buffer that overflowed; ENTRIES also stands for
+# any buffer of the base walk that a walk would have resumed from
+SLOTS, ENTRIES, FRONTIER = 1 << 9, 1 << 12, 1 << 15
+
+
+@pytest.mark.parametrize("runs,between,only_z,buffer", [(30, b"a", False, SLOTS), (56, b"z", True, FRONTIER)])
+def test_buffers_that_overflow(runs, between, only_z, buffer, gpu_mod, oracle_lib):
+    """Sequences whose rows have more origins than slots, or whose lexeme in
+    progress has more frontier entries than fit: verdict 2 and
+    EPIC_DEV_CAPACITY, and the walks that a workgroup makes after such a one
+    (more candidates than chart slots) agree with the oracle, as do the
+    selections of the other sequences."""
+    from paper_2606_00722_amd import epic
+    from tests.util import custom_vocab
+
+    lang = pairs_language(only_z)
+    vocab = custom_vocab(lang, ["ab", "zz", "ca"])
+    idx = {s: i for i, s in enumerate(vocab.strings)}
+    n = 116
+    full = masked_runs(idx, runs, between, n, between)
+    rng = np.random.default_rng(23)
+    some = np.full((3, n), idx[between], np.int32)
+    some[1] = rng.integers(0, vocab.size, n)
+    for b in range(3):
+        some[b, rng.choice(n, 4, replace=False)] = W.MASK
+    x = np.concatenate([full[None], some])
+    at = np.argwhere(some == W.MASK)
+    half = 1024  # as many walks as run at once at most: every workgroup meets the overflow first
+    seq = np.concatenate([np.zeros(half), 1 + np.resize(at[:, 0], half)]).astype(np.int32)
+    pos = np.concatenate([np.full(half, 2 * (runs - 1)), np.resize(at[:, 1], half)]).astype(np.int32)
+    tok = np.concatenate([np.full(half, idx[between]), rng.integers(0, vocab.size, half)]).astype(np.int32)
+    p = oracle_lib.problem_from(lang, vocab)
+    want = oracle_lib.validate_batch(p, x, seq[half:], pos[half:], tok[half:], NTH)
+    assert 0 < int(want.sum()) < half
+    g = gpu_mod.Gpu(W.arrays(lang, vocab), len(x), n, 2 * half)
+    out = g.torch.full((2 * half,), 7, dtype=g.torch.uint8, device=g.dev)
+    g.ctx.validate_noalloc(g.t(x), g.t(seq), g.t(pos), g.t(tok), out)
+    g.torch.cuda.synchronize()
+    assert g.errors() == epic.DEV_CAPACITY | buffer
+    for got in (out.cpu().numpy(), g.validate(x, seq, pos, tok)):
+        assert np.all(got[:half] == 2) and np.array_equal(got[half:], want)
+    assert g.errors() & ~(buffer | ENTRIES) == epic.DEV_CAPACITY
+    # the selection: two candidates of the first sequence taken as valid
+    first = np.unique(at[:, 0] * n + at[:, 1], return_index=True)[1]
+    v = want[first]
+    seq2 = np.concatenate([[0, 0], seq[half:][first]]).astype(np.int32)
+    pos2 = np.concatenate([[0, 2], pos[half:][first]]).astype(np.int32)
+    tok2 = np.concatenate([[idx[between]] * 2, tok[half:][first]]).astype(np.int32)
+    conf = rng.random(len(seq2), dtype=np.float32)
+    want_s, _, st = oracle_lib.select(p, x, seq2[2:], pos2[2:], tok2[2:], conf[2:], v, NTH)
+    sel, _ = g.select(x, seq2, pos2, tok2, conf, np.concatenate([[1, 1], v]).astype(np.uint8))
+    assert st == 0 and g.errors() & ~(buffer | ENTRIES) == epic.DEV_CAPACITY
+    assert not sel[:2].any() and np.array_equal(sel[2:], want_s)
