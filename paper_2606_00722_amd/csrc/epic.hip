@@ -37,7 +37,6 @@ namespace epic {
 // walks then reload their table pointers from there.
 #define EPIC_DEV __device__ inline __attribute__((always_inline))
 #define EPIC_INLINE EPIC_DEV
-#define EPIC_NOINLINE
 
 __device__ inline int tid() { return (int)threadIdx.x; }
 __device__ inline int nthreads() { return (int)blockDim.x; }
@@ -49,7 +48,6 @@ __device__ inline uint64_t at_or64(uint64_t* p, uint64_t v) {
 __device__ inline int at_add32(int32_t* p, int v) { return atomicAdd(p, v); }
 __device__ inline unsigned long long at_add64(unsigned long long* p, unsigned long long v) { return atomicAdd(p, v); }
 __device__ inline uint32_t at_cas32(uint32_t* p, uint32_t cmp, uint32_t val) { return atomicCAS(p, cmp, val); }
-__device__ inline int at_min32(int32_t* p, int v) { return atomicMin(p, v); }
 // lane groups: G consecutive lanes of a wavefront (G a power of two <= 64)
 __device__ inline uint32_t grp_shfl(uint32_t v, int src, int G) { return (uint32_t)__shfl((int)v, src, G); }
 // OR over the group by DPP lane permutations within a row of 16 lanes (swap
@@ -75,8 +73,9 @@ __device__ inline uint64_t grp_or64(uint64_t v) {
 
 // Threads per walk.  A walk waits more than it computes, and its passes over
 // slots and chart entries are dealt to wavefronts, so 1024 threads (128
-// vector registers a lane) pay where rows are dense enough to feed them, which
-// depends on the masks; the host knows only the length.
+// vector registers a lane; 16-word walks then keep 32 to 72 more in scratch, for
+// their outer loops) pay where rows are dense enough to feed them, which depends
+// on the masks; the host knows only the length.
 //  * Item sets of up to four words: 1024.  Against 512, validation + selection
 //    of a step: SMILES-like 16 x 256 5.98 -> 5.72 ms, 4 x 512 18.8 -> 16.1,
 //    arith 4 x 512 13.3 -> 11.4, JSON-like 8 x 128 2.64 -> 2.60; sparse rows
@@ -90,9 +89,10 @@ __device__ inline uint64_t grp_or64(uint64_t v) {
 //    sparse rows behind the snapshot (24 x 640 3.50 ms against 3.71, 24 x 512
 //    3.44 against 3.68); masks everywhere would gain from 1024 (4 x 512 47.8
 //    against 37.5).
-//  * 16 words, validation without a workspace: 1024.  Every walk starts at the
-//    first token there, and blocks lose 1 to 3 % (12 x 640 16.5 -> 16.8 ms, 4 x
-//    1024 7.95 -> 8.16) where masks everywhere gain 20 % (4 x 512 44.5 -> 35.2).
+//  * 16 words, walks that all start at the first token (validation without a
+//    workspace; more sequences than base records): 1024.  Blocks lose 1 to 3 %
+//    (12 x 640 16.5 -> 16.8 ms, 4 x 1024 7.95 -> 8.16) where masks everywhere
+//    gain 20 % (4 x 512 44.5 -> 35.2).
 //  * 8 words, which no workload has: 512.
 constexpr int kThreads = 512;
 constexpr int kThreadsWide = 1024;
@@ -207,16 +207,6 @@ EPIC_INLINE void resume_from_base(Tab& tb, Lds<W>& L, const WsArgs& a, int rec, 
   __syncthreads();
 }
 
-// Base walks: sequence b as given, recording its state at every masked run.
-// Block b < B walks the Earley graph into base record b; block B + b (when
-// launched) walks the cover graph into base record base_slots + b (the two
-// graphs can differ: a node lives when its row, or its cover set, is not
-// empty).  A record left by an earlier call of the same context (owner tag)
-// is reused: the walk state at a masked run depends only on the tokens before
-// it, so the walk resumes at the last recorded run that starts at or before
-// the first token that differs from the sequence the record was walked on
-// (the token there is then walked as the sequence now has it), and a record
-// of the very same sequence is kept as it is.
 // A walk to be made (see walk()): its chart, and where it starts.
 struct WalkPlan {
   WgWork wk;
@@ -229,6 +219,17 @@ EPIC_INLINE int run_walk(Tab& tb, Lds<W>& L, const WalkPlan& p, int n) {
   return walk<W>(tb, L, p.wk, n, p.cover, p.i0, p.resume, p.snap, p.run0);
 }
 
+// Base walks: sequence b as given, recording its state at every masked run.
+// Block b < B walks the Earley graph into base record b; block B + b (when
+// launched) walks the cover graph into base record base_slots + b (the two
+// graphs can differ: a node lives when its row, or its cover set, is not
+// empty).  A record left by an earlier call of the same context (owner tag)
+// is reused: the walk state at a masked run depends only on the tokens before
+// it, so the walk resumes at the last recorded run that starts at or before
+// the first token that differs from the sequence the record was walked on
+// (the token there is then walked as the sequence now has it), and a record
+// of the very same sequence is kept as it is.
+//
 // Prepare base walk number blk (blk < B: the Earley graph of sequence blk;
 // else the cover graph of sequence blk - B).  With a nonzero epoch the record's
 // progress is published for walks of the same launch (publish_record).
@@ -1342,8 +1343,8 @@ epic_status upload(epic_ctx* c) {
   const HostTables& H = c->H;
   std::vector<char> blob;
   size_t o_trans = place(blob, H.trans), o_accept = place(blob, H.accept), o_ext = place(blob, H.ext),
-         o_flush = place(blob, H.flushlab), o_cexit = place(blob, H.cls_exit), o_cint = place(blob, H.cls_internal),
-         o_centry = place(blob, H.cls_entry), o_cflush = place(blob, H.cls_flush), o_expt = place(blob, H.exp_t),
+         o_flush = place(blob, H.flushlab), o_cexit = place(blob, H.cls_exit),
+         o_centry = place(blob, H.cls_entry), o_expt = place(blob, H.exp_t),
          o_comp = place(blob, H.complete), o_nsym = place(blob, H.next_sym), o_mn = place(blob, H.mn),
          o_gtm = place(blob, H.gap_tm), o_gown = place(blob, H.gap_own), o_cnt = place(blob, H.cov_nt),
          o_enib = place(blob, H.expn_nib), o_pnib = place(blob, H.pred_nib), o_gcnt = place(blob, H.gcov_nt), o_gtt = place(blob, H.gap_tt),
@@ -1396,9 +1397,7 @@ epic_status upload(epic_ctx* c) {
   t.ext = (const uint32_t*)(d + o_ext);
   t.flushlab = (const uint64_t*)(d + o_flush);
   t.cls_exit = (const uint32_t*)(d + o_cexit);
-  t.cls_internal = (const uint64_t*)(d + o_cint);
   t.cls_entry = (const uint64_t*)(d + o_centry);
-  t.cls_flush = (const uint64_t*)(d + o_cflush);
   t.exp_t = (const uint32_t*)(d + o_expt);
   t.complete = (const uint32_t*)(d + o_comp);
   t.next_sym = (const int8_t*)(d + o_nsym);
@@ -1642,7 +1641,7 @@ epic_status ValidateLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int 
     });
   } else {
     KernelTimer kt(c, kKValidate, stream);
-    with_threads<W>(n, true, [&](auto nt) {
+    with_threads<W>(n, false, [&](auto nt) {
       constexpr int NT = decltype(nt)::value;
       hipLaunchKernelGGL((validate_kernel<W, NT>), dim3(grid), dim3(NT), 0, stream, tb, seqs, B, n, cs, cp, ct, C,
                          verdict, wa);
@@ -1664,7 +1663,7 @@ epic_status SelectLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int n,
   // Alg. 4's checks resume from base walks of both graphs when validation
   // walked them (share_both); this launch resumes those records, so it walks
   // nothing when the sequences are unchanged since
-  const int share = share_both(c, B, n, C);
+  const bool share = share_both(c, B, n, C);
   if (share) launch_base<W>(c, seqs, B, n, 2 * B, wa, stream);
   {
     KernelTimer kt(c, kKSpecClear, stream);
@@ -1674,7 +1673,7 @@ epic_status SelectLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int n,
   const DevTab tb = tab_for(c, kKSelect);
   {
     KernelTimer kt(c, kKSelect, stream);
-    with_threads<W>(n, true, [&](auto nt) {
+    with_threads<W>(n, share, [&](auto nt) {
       constexpr int NT = decltype(nt)::value;
       if (share)
         hipLaunchKernelGGL((select_kernel<W, NT, true>), dim3(grid), dim3(NT), 0, stream, tb, seqs, B, n, cs, cp, ct,
@@ -1713,7 +1712,7 @@ epic_status FallbackLaunch<W>::run(epic_ctx* c, const int32_t* seqs, int B, int 
     hipLaunchKernelGGL(spec_clear_kernel<W>, dim3((B * kPlan + 255) / 256), dim3(256), 0, stream, spec, B * kPlan);
   }
   KernelTimer kt(c, kKFallback, stream);
-  with_threads<W>(n, true, [&](auto nt) {
+  with_threads<W>(n, share, [&](auto nt) {
     constexpr int NT = decltype(nt)::value;
     const DevTab tb = tab_for(c, kKFallback);
     if (share)

@@ -662,7 +662,6 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
   H.cls_exit.assign((size_t)std::max(K, 1) * QW, 0);
   H.cls_internal.assign((size_t)std::max(K * K, 1), 0);
   H.cls_entry.assign((size_t)Q * std::max(K, 1), 0);
-  H.cls_flush.assign(std::max(K, 1), 0);
   for (int r = 0; r < F; ++r) {
     int k = cls_of[r];
     if (k < 0) continue;
@@ -671,9 +670,6 @@ int build_tables(int Q, const int16_t* trans, const int16_t* accept, int T, int 
       if (cls_of[r2] >= 0) H.cls_internal[(size_t)k * K + cls_of[r2]] |= internal[r][r2];
     for (int qi = 0; qi < Q; ++qi) H.cls_entry[(size_t)qi * K + k] |= entry[qi][r];
   }
-  for (int k = 0; k < K; ++k)
-    for (int q = 0; q < Q; ++q)
-      if ((H.cls_exit[(size_t)k * QW + (q >> 5)] >> (q & 31)) & 1) H.cls_flush[k] |= H.flushlab[q];
 
   // ---------------------------------------------------------------- gap derivations
   // Inside a masked run the class nodes and their edges do not depend on the

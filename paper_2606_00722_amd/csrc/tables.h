@@ -30,7 +30,6 @@ struct HostTables {
   std::vector<uint32_t> cls_exit;       // [K*QW] lexer states in which a gap may end inside class k
   std::vector<uint64_t> cls_internal;   // [K*K] labels of edges class k -> class k'
   std::vector<uint64_t> cls_entry;      // [Q*K] labels of edges from an entry lexeme in state q into class k
-  std::vector<uint64_t> cls_flush;      // [K]
   // what a masked run derives between its class nodes (independent of the sequence)
   std::vector<uint64_t> gap_nt;   // [K*K] nonterminals deriving a path from class j to class k
   uint64_t gap_eps = 0;           // bit j*K+k: class k reachable from class j by epsilon edges
