@@ -155,7 +155,11 @@ epic_status epic_memo_export(const epic_ctx* ctx, void* host_dst, size_t bytes);
  * position out of range, position not masked in x_b, token out of range).
  * d_seqs: int32 [B*n] row-major, -1 = MASK.  d_cand_*: int32 [C].
  * d_verdict: uint8 [C].  Every candidate is judged against the same x_b.
- * d_workspace: at least epic_workspace_bytes(ctx) bytes. */
+ * d_workspace: at least epic_workspace_bytes(ctx) bytes.
+ * A launch that shares prefixes carries the number of the call, by which its
+ * walks wait for records of this very call: a HIP graph that captured the call
+ * repeats the number, so it must not be replayed on other sequences
+ * (epic_validate_batch_noalloc can be). */
 epic_status epic_validate_batch(epic_ctx* ctx, const int32_t* d_seqs, int32_t B, int32_t n,
                                 const int32_t* d_cand_seq, const int32_t* d_cand_pos,
                                 const int32_t* d_cand_tok, int32_t C, uint8_t* d_verdict,
