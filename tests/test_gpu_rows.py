@@ -115,8 +115,8 @@ def test_base_walks_of_wide_calls(B, props, graphs, gpu_mod, oracle_lib):
 @pytest.mark.parametrize("name", ["tiny_paren", "tiny_expr", "tiny_ab"])
 def test_long_rows_of_tiny_languages(name, gpu_mod, oracle_lib):
     """Nullable productions and a three-class lexer (completion by iteration)
-    with every other token masked: verdicts of every masked position and token
-    equal the oracle's."""
+    with every other token masked: the verdicts of 40 masked positions, a token
+    each, equal the oracle's."""
     from tests.util import custom_vocab
 
     lang = G.language(name)
